@@ -305,6 +305,8 @@ int gmg::setup_impl(const gmg_params* p, void* stream, gmg_ctx** out, bool field
   const LevelBuf& L0 = c->lev[0];
   c->max_partials = 2 * std::max(gmg::stencil_blocks(L0.nx, L0.ny, nz),
                                  gmg::line_blocks(L0.nx, L0.ny));
+  if ((int64_t)L0.nx * L0.ny <= gmg::kBlockMaxCols)
+    c->max_partials = std::max(c->max_partials, 2 * gmg::block_count(L0.nx, L0.ny));
   if ((e = dmalloc(&c->partials, c->max_partials + 8)) ||  // + scalar slots
       (e = dmalloc(&c->state, 1)) ||
       (e = hipHostMalloc((void**)&c->hstate, sizeof(CgState), hipHostMallocDefault)) ||
@@ -395,6 +397,9 @@ hipError_t timed(gmg_ctx* c, int kind, int level, int prec, hipStream_t s, F&& l
   return hipSuccess;
 }
 
+// whether a launch of one of the kinds would be timed now
+bool timing_any(const gmg_ctx* c, uint32_t kinds) { return c->timing && (c->timing_mask & kinds); }
+
 int drain_timing(gmg_ctx* c) {
   for (const gmg_timed_launch& t : c->pending) {
     HIP_TRY(hipEventSynchronize(t.b));
@@ -470,21 +475,37 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
                   [&](gmg::Shape sh) { return gmg::launch_smooth<T>(V0, f0, u0, ualt0, rho, s, sh); }));
   cur[0] = ualt0;
   // descend
+  bool solved = false;  // the level's first step came with the restriction
   for (int d = 0; d < L; ++d) {
     const Lvl<T> V = gmg::view<T>(c, d);
     LevelBuf& B = c->lev[d];
-    if (d > 0) {
+    if (d > 0 && !solved) {
       HIP_TRY(timed(c, GMG_K_LINE_SOLVE, d, P, s, [&](gmg::Shape sh) {
         return gmg::launch_line_solve_scaled<T>(V, fl[d], static_cast<T*>(B.u), rho, s, sh);
       }));
-      cur[d] = static_cast<T*>(B.u);
     }
+    if (d > 0) cur[d] = static_cast<T*>(B.u);
     if (d == L - 1) {
       T* other = cur[d] == B.u ? static_cast<T*>(B.ualt) : static_cast<T*>(B.u);
       HIP_TRY(smooth_steps<T>(c, d, fl[d], cur[d], other, c->p.ncoarse - 1, rho, s, &cur[d]));
     } else {
       const Lvl<T> C = gmg::view<T>(c, d + 1);
       T* fc = static_cast<T*>(c->lev[d + 1].f);
+      // onto a small level: one kernel restricts the residual and takes the
+      // level's first smoothing step (as two while either of them is timed)
+      solved = gmg::block_fits(gmg::BlockOp::RESTRICT_SOLVE, C) &&
+               !timing_any(c, (1u << GMG_K_RESIDUAL_RESTRICT) | (1u << GMG_K_LINE_SOLVE));
+      if (solved) {
+        gmg::BlockArgs<T> q;
+        q.a = cur[d];
+        q.f = fl[d];
+        q.o1 = fc;
+        q.o = static_cast<T*>(c->lev[d + 1].u);
+        q.rho = rho;
+        q.X = V;
+        HIP_TRY(gmg::launch_block<T>(gmg::BlockOp::RESTRICT_SOLVE, C, q, s));
+        continue;
+      }
       HIP_TRY(timed(c, GMG_K_RESIDUAL_RESTRICT, d, P, s, [&](gmg::Shape sh) {
         return gmg::launch_resrestrict<T>(V, C, cur[d], fl[d], fc, s, sh);
       }));
@@ -497,8 +518,11 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
     T* other = (d == 0) ? u0
                         : (cur[d] == c->lev[d].u ? static_cast<T*>(c->lev[d].ualt)
                                                  : static_cast<T*>(c->lev[d].u));
-    const int fold = c->shape[gmg::tslot(GMG_K_PROLONG_SMOOTH, d, P)].rows;
-    if (fold == 2 || fold == 3) {
+    // unless a launch shape says otherwise the prolongation is folded into the
+    // post-smoother (as two kernels while either of them is timed)
+    const gmg::Shape fold = c->shape[gmg::tslot(GMG_K_PROLONG_SMOOTH, d, P)];
+    if (fold.set ? fold.rows == 2 || fold.rows == 3
+                 : !timing_any(c, (1u << GMG_K_PROLONGATE) | (1u << GMG_K_SMOOTH))) {
       // one kernel: smooth u + P u_c without storing it
       HIP_TRY(timed(c, GMG_K_PROLONG_SMOOTH, d, P, s, [&](gmg::Shape sh) {
         return gmg::launch_prolong_smooth<T>(V, C, fl[d], cur[d], cur[d + 1], other, rho, s, sh);
@@ -836,7 +860,7 @@ int tune_kind(gmg_ctx* c, int kind, int level, int prec, Cand cand, int nti, int
     const int rows = rows_c[q0];
     for (int group : kTuneGroups) {
       if (group >= nti || (rows == 1 && group != 0)) continue;
-      const gmg::Shape sh{rows, group};
+      const gmg::Shape sh{rows, group, true};
       HIP_TRY(launch(sh));  // warm-up
       HIP_TRY(hipEventRecord(ea, s));
       for (int q = 0; q < reps; ++q) HIP_TRY(launch(sh));
@@ -922,13 +946,13 @@ int tune_levels(gmg_ctx* c, int reps, hipStream_t s, hipEvent_t ea, hipEvent_t e
         return st;
       // the prolongation folded into the post-smoother: kept where it beats
       // the two kernels
-      Shape fused{4, 0};
+      Shape fused{4, 0, true};
       float best_ms = ms_smooth + ms_prol;
       for (int q0 = 0; q0 < 2 * (int)(sizeof(kTuneGroups) / sizeof(int)); ++q0) {
         // rows 2: one wavefront per column; rows 3: two (where the level fits)
         const int group = kTuneGroups[q0 >> 1];
         if (group >= ntl) continue;
-        const Shape sh{(q0 & 1) ? 3 : 2, group};
+        const Shape sh{(q0 & 1) ? 3 : 2, group, true};
         auto go = [&] { return gmg::launch_prolong_smooth<T>(V, C, x2, x0, uc, x1, rho, s, sh); };
         HIP_TRY(go());  // warm-up
         HIP_TRY(hipEventRecord(ea, s));
@@ -1283,7 +1307,7 @@ int gmg_set_launch(gmg_ctx* c, int kernel, int level, int prec, int rows, int gr
                 rows);
   }
   if (group < 0 || group > 4096) return fail(GMG_EINVAL, "group must be in [0, 4096]");
-  c->shape[gmg::tslot(kernel, level, prec)] = gmg::Shape{rows, group};
+  c->shape[gmg::tslot(kernel, level, prec)] = gmg::Shape{rows, group, true};
   drop_graphs(c);  // captured launches carry the old shape
   return GMG_OK;
 }

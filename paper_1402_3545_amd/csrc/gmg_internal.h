@@ -108,9 +108,14 @@ struct LevelBuf {
 struct Shape {
   int rows = 4;
   int group = 0;
+  bool set = false;  // by the caller (gmg_set_launch) or the autotuner
 };
 
 constexpr int kMaxLevels = 20;
+
+// largest number of columns of a level whose smoothers take the block form
+// (line_block.h)
+constexpr int64_t kBlockMaxCols = 16384;
 
 // Slot of (kernel kind, level, precision) in the per-context tables.
 inline size_t tslot(int kind, int level, int prec) {
@@ -208,6 +213,52 @@ enum class Stencil { SPMV = 0, RESIDUAL = 1, RESIDUAL_NORM = 2, RESIDUAL_NORM_DO
 template <typename T>
 hipError_t launch_stencil(const Lvl<T>& L, Stencil mode, const T* x, const T* f, T* y,
                           float* ydown, double* partials, int64_t* nblocks, hipStream_t s, Shape sh = {});
+
+// Line kernels for levels with few columns (line_block.hip): a workgroup of
+// eight wavefronts per 8, 16 or 32 columns.
+enum class BlockOp {
+  SOLVE = 0,           // o = rho M^-1 a
+  SMOOTH = 1,          // o = a + rho M^-1 (f - A a)
+  SMOOTH_NORM = 2,     // ... and ||f - A a||^2 per workgroup
+  PROLONG_SMOOTH = 3,  // SMOOTH of a + P uc (X: the coarse level)
+  RESTRICT_SOLVE = 4,  // o1 = R (f - A a) from the finer level X, o = rho M^-1 o1
+  CG = 5               // o1 -= alpha a, o = M^-1 o1, <o1, o1>, <o1, o>
+};
+
+template <typename T>
+struct BlockArgs {
+  const T* a = nullptr;
+  const T* f = nullptr;
+  T* o = nullptr;
+  T* o1 = nullptr;
+  T rho = T(1);
+  Lvl<T> X{};
+  const T* uc = nullptr;
+  const CgState* st = nullptr;
+  int init = 0;  // CG: alpha = 0
+  double* partials = nullptr;
+};
+
+// workgroups of a level
+int64_t block_count(int nx, int ny);
+template <typename T>
+hipError_t launch_block(BlockOp op, const Lvl<T>& L, const BlockArgs<T>& a, hipStream_t s);
+
+// Whether level L (RESTRICT_SOLVE: the coarse level) is small enough for the
+// operation's block form.  The other forms solve a column in two lanes, which
+// only pays once the level's columns fill the GPU; measured on MI355X, FP64,
+// 128 layers, in us, block form / other form: Smooth 64^2 9.4 / 22.9, 128^2
+// 21 / 24, 256^2 84 / 57; line solve 64^2 8.4 / 12.4, 128^2 16 / 13; residual
+// + restriction + line solve onto 64^2 10 / 24, onto 128^2 48 / 45 (64 layers:
+// 25 / 34), onto 256^2 183 / 150.  Fields must stay within 32-bit byte offsets.
+template <typename T>
+bool block_fits(BlockOp op, const Lvl<T>& L) {
+  const int64_t cols = (int64_t)L.nx * L.ny;
+  const int64_t most =
+      op == BlockOp::SOLVE || op == BlockOp::CG ? kBlockMaxCols / 2 : kBlockMaxCols;
+  // the finer level of RESTRICT_SOLVE has at most four times the bytes
+  return cols <= most && (int64_t)L.ny * L.nz * L.ldx * (int64_t)sizeof(T) < (int64_t(1) << 29);
+}
 
 template <typename T>
 hipError_t launch_line_solve(const Lvl<T>& L, const T* r, T* z, hipStream_t s, Shape sh = {});

@@ -25,9 +25,7 @@
 // Workgroup ids are remapped so that each of the 8 XCDs (each with its own L2)
 // works on a contiguous band of tiles: neighbouring tiles share halo rows.
 
-#include <type_traits>
-
-#include "gmg_internal.h"
+#include "device_common.h"
 
 namespace gmg {
 
@@ -36,20 +34,6 @@ namespace {
 constexpr int KSEG = 32;        // layers per thread in stencil kernels
 constexpr int SROWS = 4;        // rows (j) per stencil workgroup, 64 columns wide
 constexpr int LROWS = 4;        // rows (j) per line workgroup, 32 columns wide
-constexpr int NTHREADS = 256;
-
-__device__ __forceinline__ int xcd_remap(int b, int n) {
-  const int x = b & 7, q = n >> 3, r = n & 7;
-  return x * q + min(x, r) + (b >> 3);
-}
-
-// A gated launch (a solver's iteration enqueued past its convergence)
-// returns at once; the flag is uniform, so whole workgroups leave together.
-template <typename T>
-__device__ __forceinline__ bool gated(const Lvl<T>& L) {
-  return L.gate && *L.gate;
-}
-
 template <typename T>
 struct Col {
   int64_t base;              // index of (i, j, 0)
@@ -80,31 +64,6 @@ __device__ __forceinline__ Col<T> load_col(const Lvl<T>& L, int i, int j) {
   return c;
 }
 
-// Sum NC per-thread values over the workgroup; thread 0 stores them to
-// partials[blockIdx.x*NC + c].  Fixed order, so results are reproducible.
-template <int NC, int NW = NTHREADS / 64>
-__device__ __forceinline__ void block_partials(double (&v)[NC], double* __restrict__ partials) {
-  __shared__ double sm[NC][NW];
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[c] += __shfl_xor(v[c], off);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) sm[c][w] = v[c];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int nw = blockDim.x >> 6;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      double s = 0.0;
-      for (int q = 0; q < nw; ++q) s += sm[c][q];
-      partials[(int64_t)blockIdx.x * NC + c] = s;
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Stencil kernels.  A workgroup is SR wavefronts; wavefront w owns grid row
 // j = tj*SR + w (wave-uniform, so the row bases of every field are scalar
@@ -124,31 +83,6 @@ struct Geo {
   bool ft;         // all 64 columns of the tile exist (wave-uniform)
   int k0, n;       // first layer and number of layers of the segment (uniform)
 };
-
-// Tile coordinates of logical workgroup b (all wave-uniform).  Tiles are
-// walked in groups of `group` tile columns: inside a group the tiles of one
-// tile row are adjacent and tile rows follow each other, so a tile's
-// east/west and north/south neighbours run within a few workgroups of it and
-// its halo rows are still in the XCD's L2.  group <= 0 or >= nti: row-major.
-// Segments of layers (kb) vary slowest.
-__device__ __forceinline__ void tile_coords(int b, int nti, int ntj, int group, int& ti, int& tj,
-                                            int& kb) {
-  const int per = nti * ntj;
-  kb = b / per;
-  int r = b - kb * per;
-  if (group <= 0 || group >= nti) {
-    tj = r / nti;
-    ti = r - tj * nti;
-    return;
-  }
-  const int gsize = group * ntj;
-  const int gi = r / gsize;
-  const int g0 = gi * group;
-  const int w = min(group, nti - g0);
-  r -= gi * gsize;
-  tj = r / w;
-  ti = g0 + (r - tj * w);
-}
 
 template <int SR, int KS = KSEG>
 __device__ __forceinline__ Geo stencil_geo(int nx, int ny, int nz, int nti, int ntj, int group,
@@ -205,46 +139,6 @@ __device__ __forceinline__ Cf<T> col_coef(const Lvl<T>& L, const Geo& g) {
   return c;
 }
 
-// Byte base of grid row j of a field (layer 0, column 0).
-template <typename T>
-__device__ __forceinline__ const char* rowc(const T* f, int j, int64_t jstride) {
-  return reinterpret_cast<const char*>(f + (int64_t)j * jstride);
-}
-template <typename T>
-__device__ __forceinline__ char* roww(T* f, int j, int64_t jstride) {
-  return reinterpret_cast<char*>(f + (int64_t)j * jstride);
-}
-
-// Load/store through a wave-uniform base and a 32-bit per-lane byte offset
-// (the saddr form of the global memory instructions).  Stores are
-// non-temporal: every output is written once and read by a later kernel, so
-// it should not displace the halo rows the L2 is holding for neighbouring
-// tiles.  ldn is the non-temporal load for fields a kernel reads exactly once
-// (no halo); fields read with horizontal neighbours use ldo.
-template <typename T>
-__device__ __forceinline__ T ldo(const char* base, uint32_t off) {
-  return *reinterpret_cast<const T*>(base + off);
-}
-template <typename T>
-__device__ __forceinline__ T ldn(const char* base, uint32_t off) {
-  return __builtin_nontemporal_load(reinterpret_cast<const T*>(base + off));
-}
-// non-temporal load of a pair (double2 / float2) as one 16- or 8-byte access
-template <typename V>
-__device__ __forceinline__ V ldn2(const char* base, uint32_t off) {
-  using E = decltype(V{}.x);
-  typedef E N2 __attribute__((ext_vector_type(2)));
-  const N2 t = __builtin_nontemporal_load(reinterpret_cast<const N2*>(base + off));
-  return V{t.x, t.y};
-}
-template <typename T>
-__device__ __forceinline__ void sto(char* base, uint32_t off, T v) {
-  if constexpr (std::is_arithmetic_v<T>)
-    __builtin_nontemporal_store(v, reinterpret_cast<T*>(base + off));
-  else
-    *reinterpret_cast<T*>(base + off) = v;
-}
-
 // The layer walk shared by the stencil kernels: P supplies the per-layer
 // input record In, load(s, In&) for layer k0+s and step(s, const In&) that
 // computes and stores layer k0+s.  FULL: the segment has all KS layers.
@@ -269,27 +163,6 @@ __device__ __forceinline__ void walk(P& pol, int n) {
     }
     // keep later chunks' loads from being hoisted further (registers)
     __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// A value from another lane of the wavefront by a DPP wave shift: CTRL
-// kWaveShl1 gives lane l the value of lane l+1, kWaveShr1 that of lane l-1
-// (the lane at the end receives 0).  Every lane of the wavefront must be
-// active.
-constexpr int kWaveShl1 = 0x130;
-constexpr int kWaveShr1 = 0x138;
-template <int CTRL, typename T>
-__device__ __forceinline__ T wave_shift(T v) {
-  if constexpr (sizeof(T) == 8) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf,
-                                                              0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL,
-                                                              0xf, 0xf, false);
-    return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
-  } else {
-    return __builtin_bit_cast(
-        T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
   }
 }
 
@@ -451,19 +324,6 @@ __global__ __launch_bounds__(64 * SR) void k_stencil(Lvl<T> L, const T* __restri
   if constexpr (MODE >= (int)Stencil::RESIDUAL_NORM) block_partials<1, SR>(nrm, partials);
 }
 
-// u + (9 a + wb b + wc c + wd d) / 16: the cell-centred bilinear correction of
-// one fine cell from its coarse parent a, x and y neighbours b, c and diagonal
-// d, with the fused multiply-adds spelled out so that every kernel that forms
-// it (the prolongation, and the smoother that folds it in) rounds the same way.
-template <typename T>
-__device__ __forceinline__ T prolong_add(T u, T a, T b, T c, T d, T wb, T wc, T wd) {
-  T p = T(9) * a;
-  p = fma(wb, b, p);
-  p = fma(wc, c, p);
-  p = fma(wd, d, p);
-  return fma(p, T(0.0625), u);
-}
-
 // ---------------------------------------------------------------------------
 // Line kernels
 // ---------------------------------------------------------------------------
@@ -491,41 +351,6 @@ struct LineArgs {
   Lvl<T> C;           // PROLONG_SMOOTH: the coarse level
   const T* uc;        // PROLONG_SMOOTH: the coarse-level correction
 };
-
-template <typename T>
-struct Vec2;
-template <>
-struct Vec2<double> { using type = double2; };
-template <>
-struct Vec2<float> { using type = float2; };
-
-// Reciprocal: hardware estimate refined by Newton-Raphson steps
-// r <- r (2 - p r), written as e = 1 - p r, r <- r + r e (two steps in FP64,
-// one in FP32 bring the estimate to the last bit or so).  Pivots here are
-// positive and well scaled, so no special cases arise.
-__device__ __forceinline__ double rcp_nr(double p) {
-  double r = __builtin_amdgcn_rcp(p);
-  double e = fma(-p, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-p, r, 1.0);
-  return fma(r, e, r);
-}
-__device__ __forceinline__ float rcp_nr(float p) {
-  const float r = __builtin_amdgcn_rcpf(p);
-  const float e = fmaf(-p, r, 1.0f);
-  return fmaf(r, e, r);
-}
-
-// One elimination step: pivot, its reciprocal and the new c' of this row.
-// The line kernels spell out every fused multiply-add, so that each kernel
-// (and the back sweep's recomputation of the forward sweep) rounds the same
-// way whatever the compiler would contract.
-template <typename T>
-__device__ __forceinline__ void elim_step(T diag, T cpv, T cnx, T cprev, T& piv, T& inv, T& c) {
-  piv = fma(-cpv, cprev, diag);
-  inv = rcp_nr(piv);
-  c = cnx * inv;
-}
 
 // Values one elimination step reads from memory (loaded a chunk ahead).
 template <typename T, int MODE>
@@ -2413,6 +2238,16 @@ bool line_w2_fits(const Lvl<T>& L) {
   return L.nx % 64 == 0 && L.ny % 2 == 0 && (L.nz == 32 || L.nz == 64 || L.nz == 128);
 }
 
+// the block form of a line kernel
+template <int MODE>
+constexpr BlockOp block_op() {
+  return MODE == LINE_SOLVE            ? BlockOp::SOLVE
+         : MODE == LINE_SMOOTH         ? BlockOp::SMOOTH
+         : MODE == LINE_SMOOTH_NORM    ? BlockOp::SMOOTH_NORM
+         : MODE == LINE_PROLONG_SMOOTH ? BlockOp::PROLONG_SMOOTH
+                                       : BlockOp::CG;
+}
+
 template <typename T, int MODE>
 hipError_t line_dispatch(const Lvl<T>& L, const LineArgs<T>& a, hipStream_t s, int group,
                          int rows = 4) {
@@ -2423,6 +2258,23 @@ hipError_t line_dispatch(const Lvl<T>& L, const LineArgs<T>& a, hipStream_t s, i
       hipLaunchKernelGGL((k_line_pcr<T, MODE>), dim3(cdiv(ncols, NTHREADS / 64)),
                          dim3(NTHREADS), 0, s, L, a, ncols);
       return hipGetLastError();
+    }
+  }
+  if constexpr (MODE != LINE_RESTRICT_SMOOTH) {
+    // levels with few columns: eight wavefronts per 32 columns
+    if (block_fits(block_op<MODE>(), L)) {
+      BlockArgs<T> q;
+      q.a = a.a;
+      q.f = a.b;
+      q.o = a.o0;
+      q.o1 = a.rw;
+      q.rho = a.rho;
+      q.X = a.C;
+      q.uc = a.uc;
+      q.st = a.st;
+      q.init = a.init;
+      q.partials = a.partials;
+      return launch_block<T>(block_op<MODE>(), L, q, s);
     }
   }
   const int nti = cdiv(L.nx, 32), ntj = cdiv(L.ny, LROWS);
@@ -2611,6 +2463,9 @@ hipError_t launch_line_solve(const Lvl<T>& L, const T* r, T* z, hipStream_t s, S
   return line_dispatch<T, LINE_SOLVE>(L, a, s, sh.group, sh.rows);
 }
 
+// Smoothers stage their neighbours in LDS unless a launch shape says otherwise.
+int smooth_rows(const Shape& sh) { return sh.set ? sh.rows : 2; }
+
 template <typename T>
 hipError_t launch_smooth(const Lvl<T>& L, const T* f, const T* uin, T* uout, T rho,
                          hipStream_t s, Shape sh) {
@@ -2619,7 +2474,7 @@ hipError_t launch_smooth(const Lvl<T>& L, const T* f, const T* uin, T* uout, T r
   a.b = f;
   a.o0 = uout;
   a.rho = rho;
-  return line_dispatch<T, LINE_SMOOTH>(L, a, s, sh.group, sh.rows);
+  return line_dispatch<T, LINE_SMOOTH>(L, a, s, sh.group, smooth_rows(sh));
 }
 
 template <typename T>
@@ -2667,9 +2522,10 @@ hipError_t launch_smooth_norm(const Lvl<T>& L, const T* f, const T* uin, T* uout
   a.o0 = uout;
   a.rho = rho;
   a.partials = partials;
-  *nblocks = (sh.rows == 3 && line_w2_fits(L)) ? (int64_t)(L.nx / 64) * (L.ny / 2)
+  *nblocks = block_fits(BlockOp::SMOOTH_NORM, L) ? block_count(L.nx, L.ny)
+             : (sh.rows == 3 && line_w2_fits(L)) ? (int64_t)(L.nx / 64) * (L.ny / 2)
                                                 : line_blocks(L.nx, L.ny);
-  return line_dispatch<T, LINE_SMOOTH_NORM>(L, a, s, sh.group, sh.rows);
+  return line_dispatch<T, LINE_SMOOTH_NORM>(L, a, s, sh.group, smooth_rows(sh));
 }
 
 // Levels with at most kShortSegCols lane columns walk segments of KSHORT
@@ -2753,7 +2609,7 @@ hipError_t launch_cg_p2(const Lvl<double>& L, double* r, const double* q, double
   a.st = st;
   a.init = init;
   a.partials = partials;
-  *nblocks = line_blocks(L.nx, L.ny);
+  *nblocks = block_fits(BlockOp::CG, L) ? block_count(L.nx, L.ny) : line_blocks(L.nx, L.ny);
   return line_dispatch<double, LINE_CG>(L, a, s, sh.group);
 }
 

@@ -307,6 +307,9 @@ int gmg::setup_impl(const gmg_params* p, void* stream, gmg_ctx** out, bool field
                                  gmg::line_blocks(L0.nx, L0.ny));
   if ((int64_t)L0.nx * L0.ny <= gmg::kBlockMaxCols)
     c->max_partials = std::max(c->max_partials, 2 * gmg::block_count(L0.nx, L0.ny));
+  // (a coarser level's segments may be shorter)
+  for (const LevelBuf& L : c->lev)
+    c->max_partials = std::max(c->max_partials, 2 * gmg::stencil_blocks(L.nx, L.ny, nz));
   if ((e = dmalloc(&c->partials, c->max_partials + 8)) ||  // + scalar slots
       (e = dmalloc(&c->state, 1)) ||
       (e = hipHostMalloc((void**)&c->hstate, sizeof(CgState), hipHostMallocDefault)) ||
@@ -519,10 +522,12 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
                         : (cur[d] == c->lev[d].u ? static_cast<T*>(c->lev[d].ualt)
                                                  : static_cast<T*>(c->lev[d].u));
     // unless a launch shape says otherwise the prolongation is folded into the
-    // post-smoother (as two kernels while either of them is timed)
+    // post-smoother where that is the faster form (as two kernels while
+    // either of them is timed)
     const gmg::Shape fold = c->shape[gmg::tslot(GMG_K_PROLONG_SMOOTH, d, P)];
     if (fold.set ? fold.rows == 2 || fold.rows == 3
-                 : !timing_any(c, (1u << GMG_K_PROLONGATE) | (1u << GMG_K_SMOOTH))) {
+                 : gmg::fold_prolongation(V) &&
+                       !timing_any(c, (1u << GMG_K_PROLONGATE) | (1u << GMG_K_SMOOTH))) {
       // one kernel: smooth u + P u_c without storing it
       HIP_TRY(timed(c, GMG_K_PROLONG_SMOOTH, d, P, s, [&](gmg::Shape sh) {
         return gmg::launch_prolong_smooth<T>(V, C, fl[d], cur[d], cur[d + 1], other, rho, s, sh);

@@ -254,8 +254,10 @@ hipError_t launch_block(BlockOp op, const Lvl<T>& L, const BlockArgs<T>& a, hipS
 template <typename T>
 bool block_fits(BlockOp op, const Lvl<T>& L) {
   const int64_t cols = (int64_t)L.nx * L.ny;
-  const int64_t most =
-      op == BlockOp::SOLVE || op == BlockOp::CG ? kBlockMaxCols / 2 : kBlockMaxCols;
+  const int64_t most = op == BlockOp::SOLVE || op == BlockOp::CG ? kBlockMaxCols / 2
+                       : op == BlockOp::PROLONG_SMOOTH && sizeof(T) == 4 && L.nz <= 64
+                           ? 2 * kBlockMaxCols
+                           : kBlockMaxCols;
   // the finer level of RESTRICT_SOLVE has at most four times the bytes
   return cols <= most && (int64_t)L.ny * L.nz * L.ldx * (int64_t)sizeof(T) < (int64_t(1) << 29);
 }
@@ -272,6 +274,14 @@ hipError_t launch_smooth(const Lvl<T>& L, const T* f, const T* uin, T* uout, T r
 template <typename T>
 hipError_t launch_prolong_smooth(const Lvl<T>& F, const Lvl<T>& C, const T* f, const T* uin,
                                  const T* uc, T* uout, T rho, hipStream_t s, Shape sh = {});
+
+// Whether the folded form is the faster one without a launch shape: FP32 levels
+// between the block forms and about 65000 columns whose tiles do not fit the
+// two-wavefront form gain nothing (one sweep with the prolongation in us,
+// folded / apart: 160 x 144 x 128 27 / 20, 300 x 300 x 100 47 / 56; FP64 160 x
+// 144 x 128 41 / 39, 464 x 288 x 128 136 / 179).
+template <typename T>
+bool fold_prolongation(const Lvl<T>& F);
 
 template <typename T>
 hipError_t launch_restrict_smooth(const Lvl<T>& C, const Lvl<T>& F, const T* rf, T* fc, T* uc,

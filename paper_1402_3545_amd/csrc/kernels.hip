@@ -233,8 +233,11 @@ struct ColumnOp {
       xe = ee ? xe_in : de;
       xw = ew ? xe_in : dw;
     }
-    const T h = c.ce * xe + c.cw * xw + c.cn * xn + c.cs * xs;
-    const T ax = (pr.dg + pr.dz * c.S) * xc - pr.dz * h + pr.sub * xm + pr.sup * xp;
+    // (every multiply-add spelled out, so that each instantiation rounds the
+    // same way)
+    const T h = fma(c.cs, xs, fma(c.cn, xn, fma(c.ce, xe, c.cw * xw)));
+    const T ax =
+        fma(pr.sup, xp, fma(pr.sub, xm, fma(fma(pr.dz, c.S, pr.dg), xc, -(pr.dz * h))));
     xm = xc;
     xc = xp;
     return ax;
@@ -281,7 +284,7 @@ struct StencilPol {
   }
 };
 
-template <typename T, int MODE, int SR>
+template <typename T, int MODE, int SR, int KS>
 __global__ __launch_bounds__(64 * SR) void k_stencil(Lvl<T> L, const T* __restrict__ x,
                                                      const T* __restrict__ f, T* __restrict__ y,
                                                      float* __restrict__ ydown,
@@ -290,9 +293,9 @@ __global__ __launch_bounds__(64 * SR) void k_stencil(Lvl<T> L, const T* __restri
   constexpr int CH = sizeof(T) == 8 ? 4 : 8;
   if (gated(L)) return;
   const Geo g =
-      stencil_geo<SR>(L.nx, L.ny, L.nz, nti, ntj, group, xcd_remap(blockIdx.x, gridDim.x));
-  __shared__ Prof<T> sp[KSEG];
-  stage_prof(L, g.k0, sp);
+      stencil_geo<SR, KS>(L.nx, L.ny, L.nz, nti, ntj, group, xcd_remap(blockIdx.x, gridDim.x));
+  __shared__ Prof<T> sp[KS];
+  stage_prof<T, KS>(L, g.k0, sp);
   double nrm[1] = {0.0};
   if (g.row && g.act) {
     const int64_t jstride = (int64_t)L.nz * L.ldx;
@@ -306,16 +309,16 @@ __global__ __launch_bounds__(64 * SR) void k_stencil(Lvl<T> L, const T* __restri
       pol.ry = roww(y, g.j, jstride);
       pol.rd = MODE == (int)Stencil::RESIDUAL_NORM_DOWN ? roww(ydown, g.j, jstride) : nullptr;
       pol.nrm = 0.0;
-      walk<CH, F>(pol, g.n);
+      walk<CH, F, KS>(pol, g.n);
       nrm[0] = pol.nrm;
     };
     if (g.ft) {
-      if (g.n == KSEG)
+      if (g.n == KS)
         run(std::true_type{}, std::true_type{});
       else
         run(std::false_type{}, std::true_type{});
     } else {
-      if (g.n == KSEG)
+      if (g.n == KS)
         run(std::true_type{}, std::false_type{});
       else
         run(std::false_type{}, std::false_type{});
@@ -1372,14 +1375,17 @@ struct CorrectPol {
       xe = v.ue + (double)v.ee;
       xw = v.uw + (double)v.ew;
     }
-    const double h = c.ce * xe + c.cw * xw + c.cn * (v.un + (double)v.en) +
-                     c.cs * (v.us + (double)v.es);
-    const double au = (pr.dg + pr.dz * c.S) * xc - pr.dz * h + pr.sub * xm + pr.sup * xp;
+    // (every multiply-add spelled out, as in ColumnOp: the grouped launches
+    // round the same way)
+    const double h = fma(c.cs, v.us + (double)v.es,
+                         fma(c.cn, v.un + (double)v.en, fma(c.ce, xe, c.cw * xw)));
+    const double au =
+        fma(pr.sup, xp, fma(pr.sub, xm, fma(fma(pr.dz, c.S, pr.dg), xc, -(pr.dz * h))));
     const double rr = v.f - au;
     const int kc = FULL ? k : min(k, nz - 1);
     sto<double>(ruo, oc8 + (uint32_t)kc * kb8, xc);
     sto<float>(rr32, oc4 + (uint32_t)kc * kb4, (float)rr);
-    nrm += rr * rr;
+    nrm = fma(rr, rr, nrm);
     xm = xc;
     xc = xp;
   }
@@ -1388,14 +1394,14 @@ struct CorrectPol {
 // CH: layers of each field loaded ahead (4 for the single-instance kernel,
 // measured 880 -> 868 us at 1024^2 x 128 at two waves per SIMD; 2 keeps the
 // grouped batched kernel at three)
-template <int SR, int CH = 2>
+template <int SR, int CH = 2, int KS = KSEG>
 __device__ __forceinline__ void correct_residual_body(
     const Lvl<double>& L, const double* __restrict__ u, const float* __restrict__ e,
     const double* __restrict__ f, double* __restrict__ uout, float* __restrict__ r32,
     double* __restrict__ partials, int nti, int ntj, int group, int b) {
-  const Geo g = stencil_geo<SR>(L.nx, L.ny, L.nz, nti, ntj, group, b);
-  __shared__ Prof<double> sp[KSEG];
-  stage_prof(L, g.k0, sp);
+  const Geo g = stencil_geo<SR, KS>(L.nx, L.ny, L.nz, nti, ntj, group, b);
+  __shared__ Prof<double> sp[KS];
+  stage_prof<double, KS>(L, g.k0, sp);
   double nrm[1] = {0.0};
   if (g.row && g.act) {
     const int64_t jst = (int64_t)L.nz * L.ldx;
@@ -1437,16 +1443,16 @@ __device__ __forceinline__ void correct_residual_body(
                       : 0.0;
       P.xc = ldo<double>(P.ru, P.oc8 + (uint32_t)g.k0 * P.kb8) +
              (double)ldo<float>(P.re, P.oc4 + (uint32_t)g.k0 * P.kb4);
-      walk<CH, FL>(P, g.n);
+      walk<CH, FL, KS>(P, g.n);
       nrm[0] = P.nrm;
     };
     if (g.ft) {
-      if (g.n == KSEG)
+      if (g.n == KS)
         run(std::true_type{}, std::true_type{});
       else
         run(std::false_type{}, std::true_type{});
     } else {
-      if (g.n == KSEG)
+      if (g.n == KS)
         run(std::true_type{}, std::false_type{});
       else
         run(std::false_type{}, std::false_type{});
@@ -1455,13 +1461,13 @@ __device__ __forceinline__ void correct_residual_body(
   block_partials<1, SR>(nrm, partials);
 }
 
-template <int SR>
+template <int SR, int KS>
 __global__ __launch_bounds__(64 * SR) void k_correct_residual(
     Lvl<double> L, const double* __restrict__ u, const float* __restrict__ e,
     const double* __restrict__ f, double* __restrict__ uout, float* __restrict__ r32,
     double* __restrict__ partials, int nti, int ntj, int group) {
   if (gated(L)) return;
-  correct_residual_body<SR, 4>(L, u, e, f, uout, r32, partials, nti, ntj, group,
+  correct_residual_body<SR, 4, KS>(L, u, e, f, uout, r32, partials, nti, ntj, group,
                                xcd_remap(blockIdx.x, gridDim.x));
 }
 
@@ -1595,17 +1601,17 @@ struct CgP1Pol {
     const uint32_t o = op.oc + layer_off<FULL>(op.k0 + s, op.nz, op.kb);
     const double zc = op.xc;
     const double az = op.apply(s, v.xp, v.xe, v.xw, v.xn, v.xs);
-    const double pn = zc + beta * v.p;
-    const double qn = az + beta * v.q;
+    const double pn = fma(beta, v.p, zc);
+    const double qn = fma(beta, v.q, az);
     // the two steps in the order of the iterations they belong to
     if constexpr (PAIR) sto<double>(ru, o, fma(alpha, v.p, fma(alpha_prev, v.p2, v.u)));
     sto<double>(rw, o, pn);
     sto<double>(rq, o, qn);
-    pq += pn * qn;
+    pq = fma(pn, qn, pq);
   }
 };
 
-template <int SR, bool PAIR>
+template <int SR, bool PAIR, int KS>
 __global__ __launch_bounds__(64 * SR) void k_cg_p1(Lvl<double> L, double* __restrict__ u,
                                                    const double* __restrict__ pr,
                                                    double* __restrict__ pw,
@@ -1618,9 +1624,9 @@ __global__ __launch_bounds__(64 * SR) void k_cg_p1(Lvl<double> L, double* __rest
   constexpr int CH = 2;
   const double alpha = st->alpha, alpha_prev = st->alpha_prev, beta = st->beta;
   const Geo g =
-      stencil_geo<SR>(L.nx, L.ny, L.nz, nti, ntj, group, xcd_remap(blockIdx.x, gridDim.x));
-  __shared__ Prof<double> sp[KSEG];
-  stage_prof(L, g.k0, sp);
+      stencil_geo<SR, KS>(L.nx, L.ny, L.nz, nti, ntj, group, xcd_remap(blockIdx.x, gridDim.x));
+  __shared__ Prof<double> sp[KS];
+  stage_prof<double, KS>(L, g.k0, sp);
   double pq[1] = {0.0};
   if (g.row && g.act) {
     const int64_t jstride = (int64_t)L.nz * L.ldx;
@@ -1638,10 +1644,10 @@ __global__ __launch_bounds__(64 * SR) void k_cg_p1(Lvl<double> L, double* __rest
       pol.alpha_prev = alpha_prev;
       pol.beta = beta;
       pol.pq = 0.0;
-      walk<CH, F>(pol, g.n);
+      walk<CH, F, KS>(pol, g.n);
       pq[0] = pol.pq;
     };
-    if (g.n == KSEG)
+    if (g.n == KS)
       run(std::true_type{});
     else
       run(std::false_type{});
@@ -1716,12 +1722,12 @@ struct FcgDirPol {
     const double az = op.apply(s, v.xp, v.xe, v.xw, v.xn, v.xs);
     // the two pending steps, in the order of their iterations
     if constexpr (PAIR) sto<double>(ru, o, fma(alpha, v.p, fma(alpha_prev, v.p2, v.u)));
-    const double pn = zc + beta * v.p;
-    const double qn = az + beta * v.q;
+    const double pn = fma(beta, v.p, zc);
+    const double qn = fma(beta, v.q, az);
     sto<double>(rw, o, pn);
     sto<double>(rq, o, qn);
-    pq += pn * qn;
-    pr += pn * v.r;
+    pq = fma(pn, qn, pq);
+    pr = fma(pn, v.r, pr);
   }
 };
 
@@ -1795,10 +1801,10 @@ struct FcgUpdPol {
   __device__ __forceinline__ void step(int s, const In& v) {
     const int kc = FULL ? k0 + s : min(k0 + s, nz - 1);
     const uint32_t o = oc + (uint32_t)kc * kb;
-    const double rn = v.r - alpha * v.q;
+    const double rn = fma(-alpha, v.q, v.r);
     sto<double>(rr, o, rn);
     if (rd) sto<float>(rd, oc4 + (uint32_t)kc * kb4, (float)rn);
-    rr2 += rn * rn;
+    rr2 = fma(rn, rn, rr2);
   }
 };
 
@@ -2401,13 +2407,58 @@ hipError_t launch_pair_reduce(PairState* ps, int* active, const double* partials
   return hipGetLastError();
 }
 
+// Levels with few workgroups of KSEG layers walk segments of KSHORT layers
+// instead: their kernels are bound by the chain of dependent loads along a
+// segment, not by bandwidth, and four times the workgroups overlap those
+// waits; on larger levels the layers read twice at the segments' ends cost
+// more.  The line differs by kernel (us, KSEG / KSHORT at the given number of
+// KSEG workgroups, FP64): residual 15 / 12 at 20, 42 / 45 at 1024; CG direction
+// 12 / 6 at 20, 18.6 / 19.5 at 256; residual + restriction 11 / 4 at 5, 53 / 45
+// at 384, 30 / 31 at 512 (128 layers), 317 / 328 at 1400; prolongation 41 / 35
+// at 1152, 50 / 48 at 1536, 75 / 75 at 2304; refinement update 10 / 5 at 20, 15
+// / 16 at 240.  The flexible-CG kernels keep KSEG: their dot products steer an
+// FP32 cycle, which magnifies another order of summation on ill-conditioned
+// columns (3.6e-8 of the solution on a flat box of 60^2 x 32).
+constexpr int KSHORT = 8;
+constexpr int kSegResidual = 128, kSegCg = 192, kSegRestrict = 1024, kSegProlong = 2048,
+              kSegCorrect = 128;
+
+// Layers of a stencil workgroup's segment on a level of nx x ny lane columns;
+// `few`: the kernel's line.
+int stencil_seg(int nx, int ny, int nz, int few) {
+  return (int64_t)cdiv(nx, 64) * cdiv(ny, SROWS) * cdiv(nz, KSEG) < few ? KSHORT : KSEG;
+}
+
+// (of the kernel with the most)
 int64_t stencil_blocks(int nx, int ny, int nz) {
-  return (int64_t)cdiv(nx, 64) * cdiv(ny, SROWS) * cdiv(nz, KSEG);
+  return (int64_t)cdiv(nx, 64) * cdiv(ny, SROWS) * cdiv(nz, stencil_seg(nx, ny, nz, kSegCg));
 }
 
 int64_t line_blocks(int nx, int ny) { return (int64_t)cdiv(nx, 32) * cdiv(ny, LROWS); }
 
-// Instantiate f with the compile-time rows of a stencil launch shape.
+// Instantiate f with the compile-time rows of a stencil launch shape and the
+// layers of a segment (short ones in the 4-row shape only).
+template <typename F>
+hipError_t with_rows(int rows, int seg, F&& f) {
+  using Seg = std::integral_constant<int, KSEG>;
+  switch (rows) {
+    case 8:
+      f(std::integral_constant<int, 8>{}, Seg{});
+      break;
+    case 16:
+      f(std::integral_constant<int, 16>{}, Seg{});
+      break;
+    default:
+      if (seg == KSHORT)
+        f(std::integral_constant<int, 4>{}, std::integral_constant<int, KSHORT>{});
+      else
+        f(std::integral_constant<int, 4>{}, Seg{});
+      break;
+  }
+  return hipGetLastError();
+}
+
+// The same with segments of KSEG layers.
 template <typename F>
 hipError_t with_rows(int rows, F&& f) {
   switch (rows) {
@@ -2428,26 +2479,26 @@ template <typename T>
 hipError_t launch_stencil(const Lvl<T>& L, Stencil mode, const T* x, const T* f, T* y,
                           float* ydown, double* partials, int64_t* nblocks, hipStream_t s,
                           Shape sh) {
-  return with_rows(sh.rows, [&](auto R) {
-    constexpr int SR = decltype(R)::value;
-    const int nti = cdiv(L.nx, 64), ntj = cdiv(L.ny, SR), nkb = cdiv(L.nz, KSEG);
+  return with_rows(sh.rows, stencil_seg(L.nx, L.ny, L.nz, kSegResidual), [&](auto R, auto K) {
+    constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
+    const int nti = cdiv(L.nx, 64), ntj = cdiv(L.ny, SR), nkb = cdiv(L.nz, KS);
     const dim3 grid(nti * ntj * nkb), block(64 * SR);
     if (nblocks) *nblocks = (int64_t)nti * ntj * nkb;
     switch (mode) {
       case Stencil::SPMV:
-        hipLaunchKernelGGL((k_stencil<T, 0, SR>), grid, block, 0, s, L, x, f, y, ydown,
+        hipLaunchKernelGGL((k_stencil<T, 0, SR, KS>), grid, block, 0, s, L, x, f, y, ydown,
                            partials, nti, ntj, sh.group);
         break;
       case Stencil::RESIDUAL:
-        hipLaunchKernelGGL((k_stencil<T, 1, SR>), grid, block, 0, s, L, x, f, y, ydown,
+        hipLaunchKernelGGL((k_stencil<T, 1, SR, KS>), grid, block, 0, s, L, x, f, y, ydown,
                            partials, nti, ntj, sh.group);
         break;
       case Stencil::RESIDUAL_NORM:
-        hipLaunchKernelGGL((k_stencil<T, 2, SR>), grid, block, 0, s, L, x, f, y, ydown,
+        hipLaunchKernelGGL((k_stencil<T, 2, SR, KS>), grid, block, 0, s, L, x, f, y, ydown,
                            partials, nti, ntj, sh.group);
         break;
       case Stencil::RESIDUAL_NORM_DOWN:
-        hipLaunchKernelGGL((k_stencil<T, 3, SR>), grid, block, 0, s, L, x, f, y, ydown,
+        hipLaunchKernelGGL((k_stencil<T, 3, SR, KS>), grid, block, 0, s, L, x, f, y, ydown,
                            partials, nti, ntj, sh.group);
         break;
     }
@@ -2463,8 +2514,18 @@ hipError_t launch_line_solve(const Lvl<T>& L, const T* r, T* z, hipStream_t s, S
   return line_dispatch<T, LINE_SOLVE>(L, a, s, sh.group, sh.rows);
 }
 
-// Smoothers stage their neighbours in LDS unless a launch shape says otherwise.
-int smooth_rows(const Shape& sh) { return sh.set ? sh.rows : 2; }
+// Form of a smoother without a launch shape: FP64 stages its neighbours in
+// LDS (rows = 2), FP32 does with two wavefronts a column where the level fits
+// (rows = 3) and loads them per lane otherwise.  One sweep in us, per lane /
+// staged / two wavefronts: FP64 256^2 x 64 29.7 / 22.9 / 25.7, 464 x 287 x 128
+// 121 / 99 / -, 200 x 120 x 50 13.6 / 14.4 / -; FP32 256^2 x 128 33.5 / 26.9 /
+// 23.5, 512 x 384 x 64 41.8 / 40.1 / 36.5, 464 x 287 x 128 57 / 61 / -, 200 x
+// 120 x 50 9.0 / 11.2 / -.
+template <typename T>
+int smooth_rows(const Lvl<T>& L, const Shape& sh) {
+  if (sh.set) return sh.rows;
+  return sizeof(T) == 8 ? 2 : line_w2_fits(L) ? 3 : 4;
+}
 
 template <typename T>
 hipError_t launch_smooth(const Lvl<T>& L, const T* f, const T* uin, T* uout, T rho,
@@ -2474,7 +2535,13 @@ hipError_t launch_smooth(const Lvl<T>& L, const T* f, const T* uin, T* uout, T r
   a.b = f;
   a.o0 = uout;
   a.rho = rho;
-  return line_dispatch<T, LINE_SMOOTH>(L, a, s, sh.group, smooth_rows(sh));
+  return line_dispatch<T, LINE_SMOOTH>(L, a, s, sh.group, smooth_rows(L, sh));
+}
+
+template <typename T>
+bool fold_prolongation(const Lvl<T>& F) {
+  return sizeof(T) == 8 || block_fits(BlockOp::PROLONG_SMOOTH, F) || line_w2_fits(F) ||
+         (int64_t)F.nx * F.ny > 65536;
 }
 
 template <typename T>
@@ -2488,7 +2555,10 @@ hipError_t launch_prolong_smooth(const Lvl<T>& F, const Lvl<T>& C, const T* f, c
   a.rho = rho;
   a.C = C;
   a.uc = uc;
-  return line_dispatch<T, LINE_PROLONG_SMOOTH>(F, a, s, sh.group, sh.rows == 3 ? 3 : 2);
+  // as for the smoothers: two wavefronts a column in FP32 unless a launch
+  // shape says otherwise (only where the level fits)
+  const int rows = sh.set ? sh.rows : sizeof(T) == 4 ? 3 : 2;
+  return line_dispatch<T, LINE_PROLONG_SMOOTH>(F, a, s, sh.group, rows == 3 ? 3 : 2);
 }
 
 template <typename T>
@@ -2522,46 +2592,33 @@ hipError_t launch_smooth_norm(const Lvl<T>& L, const T* f, const T* uin, T* uout
   a.o0 = uout;
   a.rho = rho;
   a.partials = partials;
-  *nblocks = block_fits(BlockOp::SMOOTH_NORM, L) ? block_count(L.nx, L.ny)
-             : (sh.rows == 3 && line_w2_fits(L)) ? (int64_t)(L.nx / 64) * (L.ny / 2)
+  const int rows = smooth_rows(L, sh);
+  const int64_t nb = block_fits(BlockOp::SMOOTH_NORM, L) ? block_count(L.nx, L.ny)
+             : (rows == 3 && line_w2_fits(L)) ? (int64_t)(L.nx / 64) * (L.ny / 2)
                                                 : line_blocks(L.nx, L.ny);
-  return line_dispatch<T, LINE_SMOOTH_NORM>(L, a, s, sh.group, smooth_rows(sh));
+  *nblocks = nb;
+  return line_dispatch<T, LINE_SMOOTH_NORM>(L, a, s, sh.group, rows);
 }
-
-// Levels with at most kShortSegCols lane columns walk segments of KSHORT
-// layers instead of KSEG: their kernels are bound by the chain of dependent
-// loads along a segment, not by bandwidth, and shorter segments give more
-// workgroups to overlap those waits (the FP64 residual-restriction onto
-// 64^2 and 32^2: 23 -> 12 and 19 -> 10 us; onto 128^2, which reads a 256^2
-// level, they cost 10 %).
-constexpr int KSHORT = 8;
-constexpr int64_t kShortSegCols = 64 * 64;
 
 template <typename T>
 hipError_t launch_resrestrict(const Lvl<T>& F, const Lvl<T>& C, const T* u, const T* f, T* fc,
                               hipStream_t s, Shape sh) {
-  const bool shortseg = (int64_t)C.nx * C.ny <= kShortSegCols;
-  return with_rows(sh.rows, [&](auto R) {
-    constexpr int SR = decltype(R)::value;
-    const int ks = shortseg ? KSHORT : KSEG;
-    const int nti = cdiv(C.nx, 64), ntj = cdiv(C.ny, SR), nkb = cdiv(C.nz, ks);
-    if (shortseg)
-      hipLaunchKernelGGL((k_resrestrict<T, SR, KSHORT>), dim3(nti * ntj * nkb), dim3(64 * SR), 0,
-                         s, F, C, u, f, fc, nti, ntj, sh.group);
-    else
-      hipLaunchKernelGGL((k_resrestrict<T, SR, KSEG>), dim3(nti * ntj * nkb), dim3(64 * SR), 0,
-                         s, F, C, u, f, fc, nti, ntj, sh.group);
+  return with_rows(sh.rows, stencil_seg(C.nx, C.ny, C.nz, kSegRestrict), [&](auto R, auto K) {
+    constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
+    const int nti = cdiv(C.nx, 64), ntj = cdiv(C.ny, SR), nkb = cdiv(C.nz, KS);
+    hipLaunchKernelGGL((k_resrestrict<T, SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, F, C, u, f, fc, nti, ntj,
+                       sh.group);
   });
 }
 
 hipError_t launch_correct_residual(const Lvl<double>& L, const double* u, const float* e,
                                    const double* f, double* uout, float* r32, double* partials,
                                    int64_t* nblocks, hipStream_t s, Shape sh) {
-  return with_rows(sh.rows, [&](auto R) {
-    constexpr int SR = decltype(R)::value;
-    const int nti = cdiv(L.nx, 64), ntj = cdiv(L.ny, SR), nkb = cdiv(L.nz, KSEG);
+  return with_rows(sh.rows, stencil_seg(L.nx, L.ny, L.nz, kSegCorrect), [&](auto R, auto K) {
+    constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
+    const int nti = cdiv(L.nx, 64), ntj = cdiv(L.ny, SR), nkb = cdiv(L.nz, KS);
     *nblocks = (int64_t)nti * ntj * nkb;
-    hipLaunchKernelGGL(k_correct_residual<SR>, dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, u,
+    hipLaunchKernelGGL((k_correct_residual<SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, u,
                        e, f, uout, r32, partials, nti, ntj, sh.group);
   });
 }
@@ -2569,32 +2626,26 @@ hipError_t launch_correct_residual(const Lvl<double>& L, const double* u, const 
 template <typename T>
 hipError_t launch_prolongate(const Lvl<T>& C, const Lvl<T>& F, const T* uc, T* uf,
                              hipStream_t s, Shape sh) {
-  const bool shortseg = (int64_t)F.nx * F.ny <= kShortSegCols;
-  return with_rows(sh.rows, [&](auto R) {
-    constexpr int SR = decltype(R)::value;
-    const int ks = shortseg ? KSHORT : KSEG;
-    const int nti = cdiv(F.nx, 64), ntj = cdiv(F.ny, SR), nkb = cdiv(F.nz, ks);
-    if (shortseg)
-      hipLaunchKernelGGL((k_prolongate<T, SR, KSHORT>), dim3(nti * ntj * nkb), dim3(64 * SR), 0,
-                         s, C, F, uc, uf, nti, ntj, sh.group);
-    else
-      hipLaunchKernelGGL((k_prolongate<T, SR, KSEG>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s,
-                         C, F, uc, uf, nti, ntj, sh.group);
+  return with_rows(sh.rows, stencil_seg(F.nx, F.ny, F.nz, kSegProlong), [&](auto R, auto K) {
+    constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
+    const int nti = cdiv(F.nx, 64), ntj = cdiv(F.ny, SR), nkb = cdiv(F.nz, KS);
+    hipLaunchKernelGGL((k_prolongate<T, SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, C, F, uc, uf, nti, ntj,
+                       sh.group);
   });
 }
 
 hipError_t launch_cg_p1(const Lvl<double>& L, double* u, const double* pr, double* pw,
                         const double* z, double* q, const CgState* st, bool paired,
                         double* partials, int64_t* nblocks, hipStream_t s, Shape sh) {
-  return with_rows(sh.rows, [&](auto R) {
-    constexpr int SR = decltype(R)::value;
-    const int nti = cdiv(L.nx, 64), ntj = cdiv(L.ny, SR), nkb = cdiv(L.nz, KSEG);
+  return with_rows(sh.rows, stencil_seg(L.nx, L.ny, L.nz, kSegCg), [&](auto R, auto K) {
+    constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
+    const int nti = cdiv(L.nx, 64), ntj = cdiv(L.ny, SR), nkb = cdiv(L.nz, KS);
     *nblocks = (int64_t)nti * ntj * nkb;
     if (paired)
-      hipLaunchKernelGGL((k_cg_p1<SR, true>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, u,
+      hipLaunchKernelGGL((k_cg_p1<SR, true, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, u,
                          pr, pw, z, q, st, partials, nti, ntj, sh.group);
     else
-      hipLaunchKernelGGL((k_cg_p1<SR, false>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, u,
+      hipLaunchKernelGGL((k_cg_p1<SR, false, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, u,
                          pr, pw, z, q, st, partials, nti, ntj, sh.group);
   });
 }
@@ -2609,7 +2660,9 @@ hipError_t launch_cg_p2(const Lvl<double>& L, double* r, const double* q, double
   a.st = st;
   a.init = init;
   a.partials = partials;
-  *nblocks = block_fits(BlockOp::CG, L) ? block_count(L.nx, L.ny) : line_blocks(L.nx, L.ny);
+  const int64_t nb =
+      block_fits(BlockOp::CG, L) ? block_count(L.nx, L.ny) : line_blocks(L.nx, L.ny);
+  *nblocks = nb;
   return line_dispatch<double, LINE_CG>(L, a, s, sh.group);
 }
 
@@ -2647,21 +2700,9 @@ hipError_t launch_fcg_update(const Lvl<double>& L, double* r, const double* q, f
     constexpr int SR = decltype(R)::value;
     const int nti = cdiv(L.nx, 64), ntj = cdiv(L.ny, SR), nkb = cdiv(L.nz, KSEG);
     *nblocks = (int64_t)nti * ntj * nkb;
-    hipLaunchKernelGGL(k_fcg_update<SR>, dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, r, q,
+    hipLaunchKernelGGL((k_fcg_update<SR>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, r, q,
                        rdown, st, partials, nti, ntj, sh.group);
   });
-}
-
-hipError_t launch_fcg_fin(int which, CgState* st, const double* partials, int64_t nblocks,
-                          double* hist, hipStream_t s) {
-  if (which == 0)
-    hipLaunchKernelGGL(k_fcg_fin_beta, dim3(1), dim3(NTHREADS), 0, s, st, partials, nblocks);
-  else if (which == 1)
-    hipLaunchKernelGGL(k_fcg_fin_alpha, dim3(1), dim3(NTHREADS), 0, s, st, partials, nblocks);
-  else
-    hipLaunchKernelGGL(k_fcg_fin_res, dim3(1), dim3(NTHREADS), 0, s, st, partials, nblocks,
-                       hist);
-  return hipGetLastError();
 }
 
 template hipError_t launch_fcg_zq<double>(const Lvl<double>&, const double*, const double*,
@@ -2677,6 +2718,26 @@ template hipError_t launch_fcg_dir<float>(const Lvl<double>&, const float*, doub
                                           const CgState*, bool, double*, int64_t*, hipStream_t,
                                           Shape);
 
+hipError_t launch_pcg_final_update(const Lvl<double>& L, double* u, const double* p0,
+                                   const double* p1, const CgState* st, hipStream_t s) {
+  const int64_t n = (int64_t)L.ny * L.nz * L.ldx;
+  hipLaunchKernelGGL(k_pcg_final_update, dim3(grid_stride_blocks(n)), dim3(NTHREADS), 0, s, L,
+                     u, p0, p1, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_fcg_fin(int which, CgState* st, const double* partials, int64_t nblocks,
+                          double* hist, hipStream_t s) {
+  if (which == 0)
+    hipLaunchKernelGGL(k_fcg_fin_beta, dim3(1), dim3(NTHREADS), 0, s, st, partials, nblocks);
+  else if (which == 1)
+    hipLaunchKernelGGL(k_fcg_fin_alpha, dim3(1), dim3(NTHREADS), 0, s, st, partials, nblocks);
+  else
+    hipLaunchKernelGGL(k_fcg_fin_res, dim3(1), dim3(NTHREADS), 0, s, st, partials, nblocks,
+                       hist);
+  return hipGetLastError();
+}
+
 hipError_t launch_cg_fin1(CgState* st, const double* partials, int64_t nblocks, hipStream_t s) {
   hipLaunchKernelGGL(k_cg_fin1, dim3(1), dim3(NTHREADS), 0, s, st, partials, nblocks);
   return hipGetLastError();
@@ -2686,14 +2747,6 @@ hipError_t launch_cg_fin2(CgState* st, const double* partials, int64_t nblocks, 
                           double* hist, hipStream_t s) {
   hipLaunchKernelGGL(k_cg_fin2, dim3(1), dim3(NTHREADS), 0, s, st, partials, nblocks, init,
                      hist);
-  return hipGetLastError();
-}
-
-hipError_t launch_pcg_final_update(const Lvl<double>& L, double* u, const double* p0,
-                                   const double* p1, const CgState* st, hipStream_t s) {
-  const int64_t n = (int64_t)L.ny * L.nz * L.ldx;
-  hipLaunchKernelGGL(k_pcg_final_update, dim3(grid_stride_blocks(n)), dim3(NTHREADS), 0, s, L,
-                     u, p0, p1, st);
   return hipGetLastError();
 }
 
@@ -2737,6 +2790,7 @@ hipError_t launch_add_f32_to_f64(double* u, const float* e, int64_t n, hipStream
                                        Shape);                                                \
   template hipError_t launch_prolong_smooth<T>(const Lvl<T>&, const Lvl<T>&, const T*,        \
                                                const T*, const T*, T*, T, hipStream_t, Shape);\
+  template bool fold_prolongation<T>(const Lvl<T>&);                                          \
   template hipError_t launch_restrict_smooth<T>(const Lvl<T>&, const Lvl<T>&, const T*, T*,   \
                                                 T*, T, hipStream_t, Shape);                   \
   template hipError_t launch_prolongate<T>(const Lvl<T>&, const Lvl<T>&, const T*, T*,        \
@@ -2746,7 +2800,7 @@ hipError_t launch_add_f32_to_f64(double* u, const float* e, int64_t n, hipStream
   template hipError_t launch_line_solve_scaled<T>(const Lvl<T>&, const T*, T*, T, hipStream_t, \
                                                   Shape);                                     \
   template hipError_t launch_smooth_norm<T>(const Lvl<T>&, const T*, const T*, T*, T, double*, \
-                                            int64_t*, hipStream_t, Shape);                    \
+                                            int64_t*, hipStream_t, Shape);               \
   template hipError_t launch_resrestrict<T>(const Lvl<T>&, const Lvl<T>&, const T*, const T*, \
                                             T*, hipStream_t, Shape);
 

@@ -41,6 +41,7 @@ struct Launch {
   size_t item_off;
   int nitems;
   int nblocks;
+  int cb;  // columns of a workgroup of the block forms, 0: the other forms
 };
 
 }  // namespace
@@ -100,9 +101,15 @@ namespace {
 
 // Enqueue one refinement step (parity 0: uA -> uB, 1: uB -> uA) on stream s.
 int enqueue_step(Batch* b, int parity, hipStream_t s) {
-  for (const Launch& l : b->vc)
+  for (const Launch& l : b->vc) {
+    if (l.cb) {
+      BTRY(launch_grouped_block((GKind)l.kind, l.half, l.cb, b->ditems + l.item_off, l.nitems,
+                                l.nblocks, b->dactive, b->rho, s));
+      continue;
+    }
     BTRY(launch_grouped_f32((GKind)l.kind, l.half, l.exact != 0, b->ditems + l.item_off,
                             l.nitems, l.nblocks, b->dactive, b->rho, s));
+  }
   BTRY(launch_grouped_cr(b->dcr[parity], b->cr_nitems, b->cr_nblocks, b->dactive, b->partials, s));
   BTRY(launch_pair_reduce(b->dstate, b->dactive, b->partials, b->npairs, 0, s));
   return GMG_OK;
@@ -157,17 +164,33 @@ int build(Batch* b, hipStream_t s) {
 
   // ---- V-cycle launch lists (static: every pointer is in the arenas) ----
   std::vector<GItem<float>> items;
-  auto emit = [&](GKind kind, int half, std::vector<GItem<float>>& its) {
+  auto columns = [](const std::vector<GItem<float>>& its) {
+    int64_t n = 0;
+    for (const GItem<float>& it : its) n += (int64_t)it.L.nx * it.L.ny;
+    return n;
+  };
+  // whether a launch is small enough for its block form: the line of single
+  // levels (block_fits), for the columns of the launch together
+  auto few = [&](const std::vector<GItem<float>>& its, bool prolong) {
+    if (its.empty()) return false;
+    bool fits = columns(its) <= (prolong && its[0].L.nz <= 64 ? 2 : 1) * kBlockMaxCols;
+    for (const GItem<float>& it : its) fits = fits && block_fits(BlockOp::RESTRICT_SOLVE, it.L);
+    return fits;
+  };
+  auto emit = [&](GKind kind, int half, std::vector<GItem<float>>& its, bool block = false) {
     if (its.empty()) return;
+    const int cb = block ? block_cols(columns(its)) : 0;
     // the exact-height line kernels exist for columns of 32, 64 and 128 layers
     bool exact = half >= 16;
     for (const GItem<float>& it : its) exact = exact && it.L.nz == 2 * half;
-    Launch l{(int)kind, half, exact ? 1 : 0, items.size(), (int)its.size(), 0};
+    Launch l{(int)kind, half, exact ? 1 : 0, items.size(), (int)its.size(), 0, cb};
     int blk = 0;
     for (GItem<float>& it : its) {
       it.blk0 = blk;
       int nb;
-      if (kind == GKind::LINE_SOLVE || kind == GKind::SMOOTH || kind == GKind::PROLONG_SMOOTH) {
+      if (cb) {
+        nb = (it.L.nx * it.L.ny + cb - 1) / cb;
+      } else if (kind == GKind::LINE_SOLVE || kind == GKind::SMOOTH || kind == GKind::PROLONG_SMOOTH) {
         nb = it.nti * it.ntj;
       } else if (kind == GKind::RESRESTRICT) {
         nb = it.nti * it.ntj * (int)stencil_tiles_k(it.X.nz);
@@ -198,7 +221,8 @@ int build(Batch* b, hipStream_t s) {
       std::vector<GItem<float>> sel;
       for (const GItem<float>& it : its)
         if (half_class(it.L.nz) == h) sel.push_back(it);
-      emit(kind, h, sel);
+      emit(kind, h, sel,
+           kind != GKind::LINE_SOLVE && few(sel, kind == GKind::PROLONG_SMOOTH));
     }
   };
   int Lmax = 0;
@@ -220,7 +244,7 @@ int build(Batch* b, hipStream_t s) {
     std::vector<GItem<float>> ls;
     for (int q = 0; q < b->npairs; ++q) {
       const int Lq = b->inst[b->pair_inst[q]]->nlevels;
-      if (D >= Lq) continue;
+      if (D >= Lq || (D > 0 && cur[q][D])) continue;  // (solved with the restriction)
       PairBufs& P = b->pb[q];
       float* out;
       if (D > 0) {
@@ -247,21 +271,31 @@ int build(Batch* b, hipStream_t s) {
       }
       emit_by_half(GKind::SMOOTH, sm);
     }
-    // residual restricted to the next level
+    // residual restricted to the next level; onto few columns together with
+    // that level's line solve
     std::vector<GItem<float>> rr;
-    for (int q = 0; q < b->npairs; ++q) {
-      const gmg_ctx* c = b->inst[b->pair_inst[q]];
-      if (D >= c->nlevels - 1) continue;
-      GItem<float> it{};
-      it.L = view<float>(c, D);
-      it.X = view<float>(c, D + 1);
-      it.a = cur[q][D];
-      it.b = rhs_of(q, D);
-      it.o = b->pb[q].fc[D + 1];
-      it.nti = (int)stencil_tiles_x(it.X.nx);
-      it.ntj = (int)stencil_tiles_y(it.X.ny);
-      it.pair = q;
-      rr.push_back(it);
+    for (int h : halves) {
+      std::vector<GItem<float>> rs;
+      for (int q = 0; q < b->npairs; ++q) {
+        const gmg_ctx* c = b->inst[b->pair_inst[q]];
+        if (D >= c->nlevels - 1 || half_class(c->nz) != h) continue;
+        GItem<float> it = line_item(q, D + 1, cur[q][D], rhs_of(q, D), b->pb[q].u[D + 1]);
+        it.X = view<float>(c, D);
+        it.o1 = b->pb[q].fc[D + 1];
+        rs.push_back(it);
+      }
+      if (few(rs, false)) {
+        for (const GItem<float>& it : rs) cur[it.pair][D + 1] = it.o;
+        emit(GKind::RESTRICT_SOLVE, h, rs, true);
+        continue;
+      }
+      for (GItem<float> it : rs) {
+        std::swap(it.L, it.X);  // L: the fine level
+        it.o = it.o1;
+        it.nti = (int)stencil_tiles_x(it.X.nx);
+        it.ntj = (int)stencil_tiles_y(it.X.ny);
+        rr.push_back(it);
+      }
     }
     emit(GKind::RESRESTRICT, 0, rr);
   }

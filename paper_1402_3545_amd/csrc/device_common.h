@@ -74,6 +74,19 @@ __device__ __forceinline__ void tile_coords(int b, int nti, int ntj, int group, 
   ti = g0 + (r - tj * w);
 }
 
+// The item of a grouped launch that workgroup B belongs to (sorted by their
+// first workgroups).
+template <typename I>
+__device__ __forceinline__ int find_item(const I* __restrict__ items, int nitems, int B) {
+  int lo = 0, hi = nitems - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (items[mid].blk0 <= B) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Byte base of grid row j of a field (layer 0, column 0).
 template <typename T>
 __device__ __forceinline__ const char* rowc(const T* f, int j, int64_t jstride) {

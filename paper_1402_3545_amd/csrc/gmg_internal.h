@@ -62,6 +62,7 @@ struct GItem {
   const T* b;    // smooth, resrestrict: f
   T* o;          // line: output; resrestrict: f_c; prolongate: u_f (updated)
   const T* c;    // prolong-smooth: u_c (a: u_f, b: f, o: the smoothed u_f + P u_c)
+  T* o1;         // restrict-solve: f_c (L: coarse, X: fine, a: u_f, b: f_f, o: u_c)
   int nti, ntj;  // tiles of the item
   int blk0;      // first workgroup of the item in its launch
   int pair;      // (instance, rhs) index: activity mask, partial-sum segment
@@ -239,7 +240,8 @@ struct BlockArgs {
   double* partials = nullptr;
 };
 
-// workgroups of a level
+// columns of a workgroup (line_block.h) and workgroups of a level
+int block_cols(int64_t ncols);
 int64_t block_count(int nx, int ny);
 template <typename T>
 hipError_t launch_block(BlockOp op, const Lvl<T>& L, const BlockArgs<T>& a, hipStream_t s);
@@ -248,13 +250,15 @@ hipError_t launch_block(BlockOp op, const Lvl<T>& L, const BlockArgs<T>& a, hipS
 // operation's block form.  The other forms solve a column in two lanes, which
 // only pays once the level's columns fill the GPU; measured on MI355X, FP64,
 // 128 layers, in us, block form / other form: Smooth 64^2 9.4 / 22.9, 128^2
-// 21 / 24, 256^2 84 / 57; line solve 64^2 8.4 / 12.4, 128^2 16 / 13; residual
-// + restriction + line solve onto 64^2 10 / 24, onto 128^2 48 / 45 (64 layers:
-// 25 / 34), onto 256^2 183 / 150.  Fields must stay within 32-bit byte offsets.
+// 21 / 24, 256^2 84 / 57; line solve 64^2 8.4 / 12.4, 128^2 15 / 13 (64 layers
+// 7.5 / 8.2); residual + restriction + line solve onto 64^2 10 / 24, onto 128^2
+// 48 / 45 (64 layers 25 / 34), onto 256^2 183 / 150.  Fields must stay within
+// 32-bit byte offsets.
 template <typename T>
 bool block_fits(BlockOp op, const Lvl<T>& L) {
   const int64_t cols = (int64_t)L.nx * L.ny;
-  const int64_t most = op == BlockOp::SOLVE || op == BlockOp::CG ? kBlockMaxCols / 2
+  const int64_t most = op == BlockOp::CG || (op == BlockOp::SOLVE && L.nz > 64)
+                           ? kBlockMaxCols / 2
                        : op == BlockOp::PROLONG_SMOOTH && sizeof(T) == 4 && L.nz <= 64
                            ? 2 * kBlockMaxCols
                            : kBlockMaxCols;
@@ -367,11 +371,22 @@ hipError_t launch_transpose(const T* src, T* dst, int nx, int ny, int nz, int64_
 hipError_t launch_add_f32_to_f64(double* u, const float* e, int64_t n, hipStream_t s);
 
 // grouped launches (batched solves)
-enum class GKind { LINE_SOLVE = 0, SMOOTH = 1, RESRESTRICT = 2, PROLONGATE = 3, PROLONG_SMOOTH = 4 };
+enum class GKind {
+  LINE_SOLVE = 0,
+  SMOOTH = 1,
+  RESRESTRICT = 2,
+  PROLONGATE = 3,
+  PROLONG_SMOOTH = 4,
+  RESTRICT_SOLVE = 5  // block form only
+};
 // exact: every item has columns of exactly 2 * half layers (32, 64 or 128)
 hipError_t launch_grouped_f32(GKind kind, int half, bool exact, const GItem<float>* items,
                               int nitems, int nblocks, const int* active, float rho,
                               hipStream_t s);
+// the block forms (SMOOTH, PROLONG_SMOOTH, RESTRICT_SOLVE) with cb columns a workgroup
+hipError_t launch_grouped_block(GKind kind, int half, int cb, const GItem<float>* items,
+                                int nitems, int nblocks, const int* active, float rho,
+                                hipStream_t s);
 hipError_t launch_grouped_cr(const GItemCR* items, int nitems, int nblocks, const int* active,
                              double* partials, hipStream_t s);
 // one workgroup per pair: sum its partials, update its state and activity

@@ -1856,17 +1856,6 @@ __global__ __launch_bounds__(64 * SR) void k_fcg_update(Lvl<double> L, double* _
 // workgroups (uniform scalar loads) and runs the single-level body.  Items of
 // converged pairs return at once.
 // ---------------------------------------------------------------------------
-template <typename I>
-__device__ __forceinline__ int find_item(const I* __restrict__ items, int nitems, int B) {
-  int lo = 0, hi = nitems - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (items[mid].blk0 <= B) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
 // EX: every item of the launch has columns of exactly 2 HALF layers (the host
 // checks), so the exact-height form serves them all.
 template <int HALF, int MODE, bool EX>
@@ -2389,6 +2378,8 @@ hipError_t launch_grouped_f32(GKind kind, int half, bool exact, const GItem<floa
     case GKind::PROLONGATE:
       hipLaunchKernelGGL(k_prolongate_grouped, grid, block, 0, s, items, nitems, active);
       return hipGetLastError();
+    case GKind::RESTRICT_SOLVE:
+      break;  // a block form
   }
   return hipErrorInvalidValue;
 }

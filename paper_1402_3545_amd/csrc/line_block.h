@@ -6,7 +6,7 @@
 // issue of every row's loads and arithmetic in turn.  Here eight wavefronts
 // share CB columns.  Seven form the right-hand sides of all rows at once, a few
 // rows each; meanwhile the eighth eliminates the matrix, whose pivots do not
-// depend on the right-hand side, and keeps their reciprocals in registers.
+// depend on the right-hand side, and keeps their reciprocals.
 // What is left in sequence is one multiply-add and one product a row inwards
 // and one multiply-add a row back, on values that wait in LDS; then the other
 // wavefronts store.
@@ -39,6 +39,20 @@ constexpr int kBlockThreads = 64 * kBlockWaves;
 template <typename T>
 using BlockProf = T __attribute__((ext_vector_type(4)));
 
+// Whether the reciprocal pivots and d' wait in LDS instead of registers, so that
+// two workgroups fit a compute unit where there are more than 256 of them: the
+// forms whose right-hand sides leave the room (FP64 64 layers 128^2: line solve
+// 9.3 -> 7.5 us, Smooth 12.0 -> 10.1; FP32 128 layers 128^2: 13.1 -> 11.0, 14.6
+// -> 12.9, with the prolongation 19.2 -> 17.3; the others spill and lose).
+template <typename T, int MODE, int HALF, int CB>
+constexpr bool block_lds() {
+  constexpr bool plain = MODE == (int)BlockOp::SOLVE || MODE == (int)BlockOp::SMOOTH ||
+                         MODE == (int)BlockOp::SMOOTH_NORM;
+  if (CB != 32) return false;
+  if (sizeof(T) == 4) return HALF == 64 && MODE != (int)BlockOp::RESTRICT_SOLVE;
+  return (HALF == 32 && plain) || (HALF == 64 && MODE == (int)BlockOp::SOLVE);
+}
+
 // CB: columns of the workgroup (8, 16 or 32).
 template <typename T, int MODE, int HALF, int CB>
 __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& a, int ncols,
@@ -48,6 +62,7 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
   constexpr bool kSmooth = MODE == (int)BlockOp::SMOOTH || kNorm || kPro;
   constexpr bool kRes = MODE == (int)BlockOp::RESTRICT_SOLVE;
   constexpr bool kCg = MODE == (int)BlockOp::CG;
+  constexpr bool kLds = block_lds<T, MODE, HALF, CB>();
   constexpr int NR = 2 * HALF;                            // padded rows of a column
   constexpr int LG = 64 / CB;                             // row groups of a wavefront
   constexpr int NG = LG * (kBlockWaves - 1);              // ... of the workgroup
@@ -65,6 +80,7 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
   __shared__ BlockProf<T> s_t[2][HALF + 1];
   __shared__ BlockProf<T> s_q[kRes ? NR : 1];             // the fine level's sub, sup, dg, dz
   __shared__ T s_r[NR][CB];                       // right-hand sides, d', x
+  __shared__ T s_i[kLds ? NR : 1][kLds ? CB : 1];  // reciprocal pivots (kLds)
 
   const int nz = L.nz, nx = L.nx, ny = L.ny;
   for (int q = threadIdx.x; q < NR; q += kBlockThreads) {
@@ -104,7 +120,9 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
   double acc[2] = {0.0, 0.0};
   T keep[kCg ? R : 1];  // CG: the right-hand sides, for <r, z>
   const int k0 = (LG * (w - 1) + grp) * R;  // the lane's rows
-  T inv[HALF];                            // wavefront 0: reciprocal pivots
+  T inv[kLds ? 1 : HALF];                 // wavefront 0: reciprocal pivots
+  T* const io = &s_i[kLds && hs ? NR - 1 : 0][kLds ? col : 0];
+  const int step = hs ? -CB : CB;
 
   if (w > 0) {
     const T alpha = kCg && !a.init ? (T)a.st->alpha : T(0);
@@ -352,8 +370,13 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
 #pragma unroll
       for (int t = 0; t < U; ++t) {
         T piv, c;
-        elim_step(fma(p[t].w, S, p[t].z), p[t].x, p[t].y, cprev, piv, inv[s + t], c);
+        T iv;
+        elim_step(fma(p[t].w, S, p[t].z), p[t].x, p[t].y, cprev, piv, iv, c);
         cprev = c;
+        if constexpr (kLds)
+          io[(s + t) * step] = iv;
+        else
+          inv[s + t] = iv;
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -365,35 +388,38 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
     // place; row s of the lane's half is at ro + s * step
     const BlockProf<T>* pt = s_t[hs];
     T* ro = &s_r[hs ? NR - 1 : 0][col];
-    const int step = hs ? -CB : CB;
     T d = T(0), c = T(0);
-    T rn[U], an[U];
+    T rn[U], an[U], vn[U];
+    auto pinv = [&](int s) { return kLds ? io[s * step] : inv[kLds ? 0 : s]; };
 #pragma unroll
     for (int t = 0; t < U; ++t) {
       rn[t] = ro[t * step];
       an[t] = pt[t].x;
+      vn[t] = pinv(t);
     }
     // d' stays in registers, or in LDS where it would not fit beside the pivots
-    constexpr bool kReg = sizeof(T) * HALF <= 256;
+    constexpr bool kReg = !kLds && sizeof(T) * HALF <= 256;
     T dk[kReg ? HALF : 1];
 #pragma unroll
     for (int s = 0; s < HALF; s += U) {
-      T r[U], cp[U];
+      T r[U], cp[U], iv[U];
 #pragma unroll
       for (int t = 0; t < U; ++t) {
         r[t] = rn[t];
         cp[t] = an[t];
+        iv[t] = vn[t];
       }
       if (s + U < HALF) {
 #pragma unroll
         for (int t = 0; t < U; ++t) {
           rn[t] = ro[(s + U + t) * step];
           an[t] = pt[s + U + t].x;
+          vn[t] = pinv(s + U + t);
         }
       }
 #pragma unroll
       for (int t = 0; t < U; ++t) {
-        d = fma(-cp[t], d, r[t]) * inv[s + t];
+        d = fma(-cp[t], d, r[t]) * iv[t];
         if constexpr (kReg)
           dk[s + t] = d;
         else
@@ -402,7 +428,7 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
       __builtin_amdgcn_sched_barrier(0);
     }
     // interface of the two halves: own last row x_a = d_a - c_a x_b
-    c = pt[HALF - 1].y * inv[HALF - 1];
+    c = pt[HALF - 1].y * pinv(HALF - 1);
     const T cq = __shfl_xor(c, CB), dq = __shfl_xor(d, CB);
     T x = fma(-c, dq, d) / fma(-c, cq, T(1));
     ro[(HALF - 1) * step] = x;
@@ -410,7 +436,7 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
 #pragma unroll
     for (int t = 0; t < U; ++t) {
       if (HALF - 2 - t < 0) continue;
-      an[t] = pt[HALF - 2 - t].y;
+      an[t] = pt[HALF - 2 - t].y * pinv(HALF - 2 - t);
       rn[t] = kReg ? dk[kReg ? HALF - 2 - t : 0] : ro[(HALF - 2 - t) * step];
     }
 #pragma unroll
@@ -419,14 +445,14 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
 #pragma unroll
       for (int t = 0; t < U; ++t) {
         if (s - t < 0) continue;
-        cb[t] = an[t] * inv[s - t];
+        cb[t] = an[t];
         r[t] = rn[t];
       }
 #pragma unroll
       for (int t = 0; t < U; ++t) {
         const int q = s - U - t;
         if (q < 0) continue;
-        an[t] = pt[q].y;
+        an[t] = pt[q].y * pinv(q);
         rn[t] = kReg ? dk[kReg ? q : 0] : ro[q * step];
       }
 #pragma unroll
@@ -460,13 +486,34 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
 }
 
 template <typename T, int MODE, int HALF, int CB>
-__global__ __launch_bounds__(kBlockThreads) void k_line_block(Lvl<T> L, BlockArgs<T> a,
-                                                              int ncols) {
+__global__ __launch_bounds__(kBlockThreads)
+__attribute__((amdgpu_waves_per_eu((block_lds<T, MODE, HALF, CB>()) ? 4 : 2))) void k_line_block(
+    Lvl<T> L, BlockArgs<T> a, int ncols) {
   if (gated(L)) return;
   if constexpr (MODE == (int)BlockOp::CG) {
     if (a.st->done) return;
   }
   block_body<T, MODE, HALF, CB>(L, a, ncols, xcd_remap(blockIdx.x, gridDim.x));
+}
+
+// One launch for the items of many (instance, right-hand side) pairs.
+template <int MODE, int HALF, int CB>
+__global__ __launch_bounds__(kBlockThreads)
+__attribute__((amdgpu_waves_per_eu((block_lds<float, MODE, HALF, CB>()) ? 4 : 2))) void
+k_line_block_grouped(const GItem<float>* __restrict__ items, int nitems,
+                     const int* __restrict__ active, float rho) {
+  const int B = xcd_remap(blockIdx.x, gridDim.x);
+  const GItem<float> it = items[find_item(items, nitems, B)];
+  if (!active[it.pair]) return;
+  BlockArgs<float> a{};
+  a.a = it.a;
+  a.f = it.b;
+  a.o = it.o;
+  a.o1 = it.o1;
+  a.rho = rho;
+  a.X = it.X;
+  a.uc = it.c;
+  block_body<float, MODE, HALF, CB>(it.L, a, it.L.nx * it.L.ny, B - it.blk0);
 }
 
 }  // namespace

@@ -6,9 +6,6 @@ namespace gmg {
 
 namespace {
 
-// columns of a workgroup (line_block.h)
-int block_cols(int64_t ncols) { return ncols <= 8 * 256 ? 8 : ncols <= 16 * 256 ? 16 : 32; }
-
 template <typename T, int MODE, int CB>
 hipError_t block_dispatch_cb(const Lvl<T>& L, const BlockArgs<T>& a, hipStream_t s) {
   const int ncols = L.nx * L.ny;
@@ -43,10 +40,46 @@ hipError_t block_dispatch(const Lvl<T>& L, const BlockArgs<T>& a, hipStream_t s)
 
 }  // namespace
 
+int block_cols(int64_t ncols) { return ncols <= 8 * 256 ? 8 : ncols <= 16 * 256 ? 16 : 32; }
+
 int64_t block_count(int nx, int ny) {
   const int64_t ncols = (int64_t)nx * ny;
   const int cb = block_cols(ncols);
   return (ncols + cb - 1) / cb;
+}
+
+hipError_t launch_grouped_block(GKind kind, int half, int cb, const GItem<float>* items,
+                                int nitems, int nblocks, const int* active, float rho,
+                                hipStream_t s) {
+  const dim3 grid(nblocks), block(kBlockThreads);
+#define GMG_GBLOCK(OP, H, CB)                                                                  \
+  if (half == H && cb == CB) {                                                                 \
+    hipLaunchKernelGGL((k_line_block_grouped<(int)BlockOp::OP, H, CB>), grid, block, 0, s,     \
+                       items, nitems, active, rho);                                            \
+    return hipGetLastError();                                                                  \
+  }
+#define GMG_GBLOCKS(OP)                                                                 \
+  GMG_GBLOCK(OP, 4, 8) GMG_GBLOCK(OP, 8, 8) GMG_GBLOCK(OP, 16, 8) GMG_GBLOCK(OP, 32, 8) \
+  GMG_GBLOCK(OP, 64, 8) GMG_GBLOCK(OP, 4, 16) GMG_GBLOCK(OP, 8, 16)                     \
+  GMG_GBLOCK(OP, 16, 16) GMG_GBLOCK(OP, 32, 16) GMG_GBLOCK(OP, 64, 16)                  \
+  GMG_GBLOCK(OP, 4, 32) GMG_GBLOCK(OP, 8, 32) GMG_GBLOCK(OP, 16, 32)                    \
+  GMG_GBLOCK(OP, 32, 32) GMG_GBLOCK(OP, 64, 32)
+  switch (kind) {
+    case GKind::SMOOTH:
+      GMG_GBLOCKS(SMOOTH)
+      break;
+    case GKind::PROLONG_SMOOTH:
+      GMG_GBLOCKS(PROLONG_SMOOTH)
+      break;
+    case GKind::RESTRICT_SOLVE:
+      GMG_GBLOCKS(RESTRICT_SOLVE)
+      break;
+    default:
+      break;
+  }
+#undef GMG_GBLOCKS
+#undef GMG_GBLOCK
+  return hipErrorInvalidValue;
 }
 
 template <typename T>

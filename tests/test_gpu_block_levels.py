@@ -91,3 +91,31 @@ def test_small_pcg_matches_oracle():
     assert st == st_ref == 0 and it == it_ref
     np.testing.assert_allclose(hist, hist_ref, rtol=1e-6, atol=1e-14)
     assert max_rel(ctx.from_device(ud), u_ref, np.abs(u_ref).max()) < 1e-9
+
+
+@pytest.mark.parametrize("bc_h", [0, 1])
+@pytest.mark.parametrize("nz", [9, 37, 64, 128])
+def test_batched_levels_equal_single_solves(nz, bc_h):
+    """Grouped launches whose levels are above and below the line of the block
+    forms (here 3 x 64^2 and 64 x 192 columns, then a quarter of that): the same
+    cycles as single-instance contexts."""
+    import paper_1402_3545_amd as G
+    kws = [dict(nx=nx, ny=ny, nz=nz, nlevels=L, kv=1e3, bc_h=bc_h,
+                kh=W.kh_uniform(80 + q, nx, ny), zfaces=W.quadratic_faces(nz))
+           for q, (nx, ny, L) in enumerate([(64, 64, 3), (64, 192, 2), (64, 64, 1), (40, 24, 3)])]
+    b = G.gmg_batch_setup([dict(prec_precond=1, **kw) for kw in kws], nrhs=2)
+    fh, fs, us = [], [], []
+    for q, kw in enumerate(kws):
+        for r in range(2):
+            fh.append(W.rhs(80 + q, r, kw["nx"], kw["ny"], nz))
+            fs.append(b.to_device(fh[-1], q))
+            us.append(b.empty(q))
+    it, rel, st = G.gmg_batch_solve(b, fs, us, rtol=1e-8, maxit=60)
+    assert st == 0
+    for p, u in enumerate(us):
+        ctx = G.GmgContext(prec_precond=G.GMG_F32, **kws[p // 2])
+        ud = ctx.empty()
+        it1, _, _, st1 = G.gmg_solve(ctx, ctx.to_device(fh[p]), ud, rtol=1e-8, maxit=60)
+        u1, ub = ctx.from_device(ud), b.from_device(u, p // 2)
+        assert st1 == 0 and it1 == it[p]
+        assert np.abs(u1 - ub).max() <= 1e-12 * np.abs(u1).max()

@@ -1157,8 +1157,12 @@ void par_memcpy(void* dst, const void* src, size_t n) {
 }
 
 // Pinned staging for the host transfers of gmg_solve_host: two buffers of up
-// to kStageBytes, allocated at first use.
-constexpr size_t kStageBytes = size_t(128) << 20;
+// to kStageBytes, allocated at first use.  A field of several chunks overlaps
+// the host's copy of one with the DMA of another; below 16 MiB a chunk's own
+// costs (its threads, its DMA's start) exceed what that saves.  Copies in of
+// two fields, ms, chunks of 128 / 16 / 4 MiB: 33.5 MB each 2.06 / 1.75 / 2.97,
+// 268 MB each 11.8 / 10.3 / -.
+constexpr size_t kStageBytes = size_t(16) << 20;
 
 int ensure_stage(gmg_ctx* c, size_t bytes) {
   if (c->stage_bytes) return GMG_OK;

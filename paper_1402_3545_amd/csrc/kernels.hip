@@ -166,6 +166,16 @@ __device__ __forceinline__ void walk(P& pol, int n) {
   }
 }
 
+// Whether layer k0, the first of a segment, sums its east product before its
+// west one: the first layer of a level's last, partial run of KSEG layers, in
+// tiles without the lane exchange.  Any order would do; but flexible CG and the
+// refinement hand these residuals to FP32 cycles, which on ill-conditioned
+// columns turn another last bit into a difference of 1e-9 to 1e-7 of the
+// solution, so every segment length keeps the one order.
+__device__ __forceinline__ bool east_first(int k0, int nz) {
+  return k0 % KSEG == 0 && k0 + KSEG > nz;
+}
+
 // The 7-point operator on one lane's column, rolled through registers:
 // (A x)_k = (dg_k + dz_k S) x_k - dz_k (Kh-weighted sum of the four horizontal
 // neighbours) + sub_k x_{k-1} + sup_k x_{k+1}, x_{-1} = x_{nz} = 0.
@@ -235,7 +245,9 @@ struct ColumnOp {
     }
     // (every multiply-add spelled out, so that each instantiation rounds the
     // same way)
-    const T h = fma(c.cs, xs, fma(c.cn, xn, fma(c.ce, xe, c.cw * xw)));
+    const T ew = s == 0 && !X && east_first(k0, nz) ? fma(c.cw, xw, c.ce * xe)
+                                                    : fma(c.ce, xe, c.cw * xw);
+    const T h = fma(c.cs, xs, fma(c.cn, xn, ew));
     const T ax =
         fma(pr.sup, xp, fma(pr.sub, xm, fma(fma(pr.dz, c.S, pr.dg), xc, -(pr.dz * h))));
     xm = xc;
@@ -1377,8 +1389,9 @@ struct CorrectPol {
     }
     // (every multiply-add spelled out, as in ColumnOp: the grouped launches
     // round the same way)
-    const double h = fma(c.cs, v.us + (double)v.es,
-                         fma(c.cn, v.un + (double)v.en, fma(c.ce, xe, c.cw * xw)));
+    const double ew = s == 0 && !X && east_first(k0, nz) ? fma(c.cw, xw, c.ce * xe)
+                                                         : fma(c.ce, xe, c.cw * xw);
+    const double h = fma(c.cs, v.us + (double)v.es, fma(c.cn, v.un + (double)v.en, ew));
     const double au =
         fma(pr.sup, xp, fma(pr.sub, xm, fma(fma(pr.dz, c.S, pr.dg), xc, -(pr.dz * h))));
     const double rr = v.f - au;

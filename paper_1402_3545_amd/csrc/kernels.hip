@@ -425,10 +425,20 @@ struct StepNbP2 { T un, f, ex, cv, ew; };
 template <typename T, int HALF, int MODE, bool NB = false, bool EX = false, bool W2 = false>
 __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a, int nti,
                                           int ntj, int group, int b) {
-  constexpr int NR = 2 * HALF;
   // the prolongation folded into the post-smoother (staged form only)
   constexpr bool PRO = MODE == LINE_PROLONG_SMOOTH;
   constexpr bool kSmooth = (MODE == LINE_SMOOTH || MODE == LINE_SMOOTH_NORM || PRO);
+  // BAL (FP64 smoothers without exact heights): the halves meet in the middle
+  // of the column's own rows instead of the padded ones, the sweeps end there,
+  // and no row is virtual (us, Smooth and with the prolongation: 300^2 x 100 65
+  // -> 62, 94 -> 84; 640 x 480 x 70 159 -> 130, 234 -> 160; 800 x 640 x 45 135
+  // -> 129, 221 -> 188).  The line solve and the CG step, with less to do a
+  // row, lose 3 to 7 % to the sweeps' extra selects.  FP32 keeps the padded
+  // order: on ill-conditioned columns another order of elimination moves its
+  // results by far more than their accuracy in FP64.
+  constexpr bool BAL = sizeof(T) == 8 && !EX && kSmooth;
+  const int NR = BAL ? L.nz : 2 * HALF;
+  const int m0 = BAL ? (NR + 1) / 2 : HALF;  // steps of the upward half
   static_assert(!PRO || NB, "the prolongation is folded into the staged smoother only");
   // smoothers only: horizontal neighbours through LDS instead of per-lane loads
   constexpr bool NBL = NB && kSmooth;
@@ -462,7 +472,7 @@ __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a,
   for (int q = threadIdx.x; q < 2 * HALF; q += blockDim.x) {
     const int h = q / HALF, st = q - h * HALF;
     const int k = h ? NR - 1 - st : st;
-    const bool real = k < nz;
+    const bool real = k < nz && (!BAL || k >= 0);
     const T sub = real ? L.sub[k] : T(0), sup = real ? L.sup[k] : T(0);
     T* pq = s_ps + h * PSH + 4 * st;
     pq[0] = h ? sup : sub;
@@ -477,6 +487,7 @@ __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a,
   const int wv = (int)(threadIdx.x >> 6);
   // W2: the half is the wavefront's (uniform); otherwise the lane's
   const int half = W2 ? __builtin_amdgcn_readfirstlane(wv & 1) : lane >> 5;
+  const int mh = BAL && half ? NR - m0 : m0;  // steps of the lane's half
   const int xl = W2 ? lane : (lane & 31);
   const int rt = W2 ? (wv >> 1) : wv;  // tile row of the wavefront
   const int i = ti * TCOLS + xl;
@@ -669,7 +680,7 @@ __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a,
     kk += dir;
     return k;
   };
-  auto kcl = [&](int k) { return (uint32_t)min(k, nz - 1); };
+  auto kcl = [&](int k) { return (uint32_t)(BAL ? min(max(k, 0), nz - 1) : min(k, nz - 1)); };
   auto off = [&](int k, int col) { return (uint32_t)col * ES + kcl(k) * kbytes; };
   using SI = std::conditional_t<
       W2, std::conditional_t<PRO, StepNbP2<T>, StepNb2<T>>,
@@ -795,6 +806,7 @@ __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a,
   load_cnext(cnext[0]);
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
+    if (BAL && ch * CH >= m0) break;  // uniform
     if constexpr (PRO) {
       // coarse stage: its previous contents were last read before the
       // previous chunk's fine-stage barrier
@@ -834,7 +846,11 @@ __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a,
       const int s = ch * CH + t;
       const SI& v = buf[ch & 1][t];
       bool real = true;
-      if constexpr (!EX) real = next_row(kf) < nz;
+      if constexpr (BAL) {
+        real = s < mh;
+      } else if constexpr (!EX) {
+        real = next_row(kf) < nz;
+      }
       // the step's profiles through an offset that the scheduler cannot see
       // ahead of the step (otherwise it hoists the reads of the whole
       // unrolled sweep and runs out of registers)
@@ -888,8 +904,9 @@ __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a,
       }
       T piv, inv, cn;
       elim_step(diag, cpv, cnx, cprev, piv, inv, cn);
-      dprev = fma(-cpv, dprev, rhs) * inv;
-      cprev = cn;
+      const T dn = fma(-cpv, dprev, rhs) * inv;
+      dprev = BAL && !real ? dprev : dn;
+      cprev = BAL && !real ? cprev : cn;
       dp[s] = dprev;
       if (s % G == G - 1) ckpt[s / G] = cprev;
     }
@@ -920,6 +937,7 @@ __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a,
   uint32_t bo = xo0 + (uint32_t)((HALF - 1) * dkb);
 #pragma unroll
   for (int g = NG - 1; g >= 0; --g) {
+    if (BAL && g * G >= m0) continue;  // uniform
     // rows of this segment: k_t = kseg + dir t
     int kseg = k0 + dir * (g * G);
     asm volatile("" : "+v"(kseg));
@@ -940,9 +958,12 @@ __device__ __forceinline__ void line_body(const Lvl<T>& L, const LineArgs<T>& a,
 #pragma unroll
     for (int t = G - 1; t >= 0; --t) {
       const int s = g * G + t;
-      if (s < HALF - 1) x = fma(-cseg[t], x, dp[s]);
+      if (BAL)
+        x = s < mh - 1 ? fma(-cseg[t], x, dp[s]) : x;
+      else if (s < HALF - 1)
+        x = fma(-cseg[t], x, dp[s]);
       const int k = kseg + dir * t;
-      const bool st = active && (EX || k < nz);
+      const bool st = active && (EX || (BAL ? s < mh : k < nz));
       // modes that need the right-hand side again rebuild it from the
       // elimination: rhs_k = d'_k piv_k + (coupling to the previous row) d'_{k-1}
       // (accurate to a few units of roundoff of the column's largest entry)

@@ -186,7 +186,8 @@ __device__ __forceinline__ bool east_first(int k0, int nz) {
 // layer brings lane 0 its west and lane 63 its east value (the tile's halo)
 // in the xe slot, and the other lanes their own x_k again (an L1 hit; no
 // branch, so the loads of a chunk stay one straight-line batch).
-template <typename T, typename TS = T, bool X = false>
+// RAG: the segment can be (the start of) a partial run of KSEG layers.
+template <typename T, typename TS = T, bool X = false, bool RAG = true>
 struct ColumnOp {
   const char *rx, *rxn, *rxs;
   uint32_t oc, oe, ow, kb, oh;
@@ -245,8 +246,8 @@ struct ColumnOp {
     }
     // (every multiply-add spelled out, so that each instantiation rounds the
     // same way)
-    const T ew = s == 0 && !X && east_first(k0, nz) ? fma(c.cw, xw, c.ce * xe)
-                                                    : fma(c.ce, xe, c.cw * xw);
+    const T ew = RAG && !X && s == 0 && east_first(k0, nz) ? fma(c.cw, xw, c.ce * xe)
+                                                           : fma(c.ce, xe, c.cw * xw);
     const T h = fma(c.cs, xs, fma(c.cn, xn, ew));
     const T ax =
         fma(pr.sup, xp, fma(pr.sub, xm, fma(fma(pr.dz, c.S, pr.dg), xc, -(pr.dz * h))));
@@ -264,12 +265,12 @@ __device__ __forceinline__ uint32_t layer_off(int k, int nz, uint32_t kb) {
 
 // SpMV (y = Ax) and Residual (r = f - Ax, optional ||r||^2 partials and an
 // FP32 copy of r for the mixed-precision refinement).
-template <typename T, int MODE, bool FULL, bool X>
+template <typename T, int MODE, bool FULL, bool X, bool RAG>
 struct StencilPol {
   struct In {
     T xp, xe, xw, xn, xs, f;
   };
-  ColumnOp<T, T, X> op;
+  ColumnOp<T, T, X, RAG> op;
   const char* rf;
   char *ry, *rd;
   double nrm;
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(64 * SR) void k_stencil(Lvl<T> L, const T* __restri
     const Cf<T> cf = col_coef(L, g);
     auto run = [&](auto full, auto xch) {
       constexpr bool F = decltype(full)::value, XC = decltype(xch)::value;
-      StencilPol<T, MODE, F, XC> pol;
+      StencilPol<T, MODE, F, XC, (!F || KS != KSEG)> pol;
       pol.op.init(x, g, jstride, kb, cf, sp, L.nz);
       pol.rf = MODE != (int)Stencil::SPMV ? rowc(f, g.j, jstride) : nullptr;
       pol.ry = roww(y, g.j, jstride);
@@ -1357,7 +1358,7 @@ __global__ __launch_bounds__(64 * SR) void k_resrestrict(Lvl<T> F, Lvl<T> C,
 // layer k are the neighbouring lanes' own, passed by wave shifts; ue / ee
 // then hold the halo column's u and e (lane 0: west, lane 63: east, other
 // lanes their own column).
-template <bool FULL, bool X>
+template <bool FULL, bool X, bool RAG>
 struct CorrectPol {
   struct In {
     double up, ue, uw, un, us, f;
@@ -1410,8 +1411,8 @@ struct CorrectPol {
     }
     // (every multiply-add spelled out, as in ColumnOp: the grouped launches
     // round the same way)
-    const double ew = s == 0 && !X && east_first(k0, nz) ? fma(c.cw, xw, c.ce * xe)
-                                                         : fma(c.ce, xe, c.cw * xw);
+    const double ew = RAG && !X && s == 0 && east_first(k0, nz) ? fma(c.cw, xw, c.ce * xe)
+                                                                : fma(c.ce, xe, c.cw * xw);
     const double h = fma(c.cs, v.us + (double)v.es, fma(c.cn, v.un + (double)v.en, ew));
     const double au =
         fma(pr.sup, xp, fma(pr.sub, xm, fma(fma(pr.dz, c.S, pr.dg), xc, -(pr.dz * h))));
@@ -1441,7 +1442,7 @@ __device__ __forceinline__ void correct_residual_body(
     const int64_t jst = (int64_t)L.nz * L.ldx;
     auto run = [&](auto full, auto xch) {
       constexpr bool FL = decltype(full)::value, XC = decltype(xch)::value;
-      CorrectPol<FL, XC> P;
+      CorrectPol<FL, XC, (!FL || KS != KSEG)> P;
       P.ru = rowc(u, g.j, jst);
       P.run = rowc(u, g.jn, jst);
       P.rus = rowc(u, g.js, jst);
@@ -1609,12 +1610,12 @@ __global__ __launch_bounds__(64 * SR) void k_prolongate(Lvl<T> C, Lvl<T> F,
 // not yet applied, u += alpha_prev p_{i-2} + alpha p_{i-1}, with p_{i-2} read
 // from the buffer that p_i then overwrites; odd iterations touch neither u nor
 // p_{i-2} (5 words per cell instead of 7; even ones 8).
-template <bool FULL, bool PAIR>
+template <bool FULL, bool PAIR, bool RAG>
 struct CgP1Pol {
   struct In {
     double xp, xe, xw, xn, xs, p, q, u, p2;
   };
-  ColumnOp<double> op;  // on z
+  ColumnOp<double, double, false, RAG> op;  // on z
   char *ru, *rw, *rq;
   const char* rp;
   double alpha, alpha_prev, beta, pq;
@@ -1668,7 +1669,7 @@ __global__ __launch_bounds__(64 * SR) void k_cg_p1(Lvl<double> L, double* __rest
     const Cf<double> cf = col_coef(L, g);
     auto run = [&](auto full) {
       constexpr bool F = decltype(full)::value;
-      CgP1Pol<F, PAIR> pol;
+      CgP1Pol<F, PAIR, (!F || KS != KSEG)> pol;
       pol.op.init(z, g, jstride, kb, cf, sp, L.nz);
       pol.ru = PAIR ? roww(u, g.j, jstride) : nullptr;
       pol.rp = rowc(pr, g.j, jstride);
@@ -1731,7 +1732,7 @@ struct FcgDirPol {
   struct In {
     double xp, xe, xw, xn, xs, p, q, r, u, p2;
   };
-  ColumnOp<double, TZ> op;  // on z
+  ColumnOp<double, TZ, false, !FULL> op;  // on z
   char *rw, *rq, *ru;
   const char *rp, *rr;
   uint32_t oc, kb;

@@ -82,14 +82,14 @@ MEASURED_TRAFFIC = {
     # launch shape); profiles/cg_p1_1024x1024x128_pmc.md.  Averages over the
     # 162 dispatches that did the work (82 odd-iteration, 80 even-iteration
     # forms; the two enqueued past convergence return at once).  Plain-copy
-    # calibration: 2 GiB read + 2 GiB written read FETCH_SIZE 1048592.3 KiB,
-    # WRITE_SIZE 2097192.6 KiB.
+    # calibration: 2 GiB read + 2 GiB written read FETCH_SIZE 1048592.2 KiB,
+    # WRITE_SIZE 2097190.1 KiB.
     ("cg_spmv", 0, "f64"): {
-        "fetch_kib": 2249939.0212,
-        "write_kib": 2615226.2820,
-        "copy_fetch_scale": 2097152.0 / 1048592.3438,
-        "copy_write_scale": 2097152.0 / 2097192.5625,
-        "source_sha256": "dd7b0d13b8c51558879fab40ede78327423d077c36128b4dd5adb5d4bc1ea7cd",
+        "fetch_kib": 2250610.1103,
+        "write_kib": 2615228.0239,
+        "copy_fetch_scale": 2097152.0 / 1048592.2292,
+        "copy_write_scale": 2097152.0 / 2097190.0625,
+        "source_sha256": "33deb66ef0d558f60261bbba4bdfcf11511fb4388749041395755f3b24f6967a",
         "shape": [8, 8],
     },
 }

@@ -226,7 +226,10 @@ int gmg_batch_solve(gmg_ctx *c, const double *const *f, double *const *u, double
  * GMG_K_LINE_SOLVE of that level.  GMG_K_PROLONG_SMOOTH is the V-cycle's
  * prolongation onto a level folded into that level's post-smoother (one
  * kernel instead of GMG_K_PROLONGATE + GMG_K_SMOOTH; timed under the fine
- * level), used where its launch shape says so (below). */
+ * level), used where its launch shape says so or, without one, where it is
+ * the faster form.  On levels with few columns the restriction takes that line
+ * solve along and the prolongation is folded; while one of the kinds is being
+ * timed, the parts run as kernels of their own (the same results bitwise). */
 typedef enum {
   GMG_K_SPMV = 0, GMG_K_RESIDUAL = 1, GMG_K_LINE_SOLVE = 2, GMG_K_SMOOTH = 3,
   GMG_K_RESTRICT_SMOOTH = 4, GMG_K_PROLONGATE = 5, GMG_K_CG_SPMV = 6, GMG_K_CG_TRIDIAG = 7,
@@ -303,13 +306,18 @@ int gmg_solve_host(gmg_ctx *c, int method, const double *f_host, double *u_host,
  *           and rows = 3: the same staging with the two halves of each column
  *           in two wavefronts (tiles of 64 columns by 2 grid rows), for
  *           levels with n_z of 32, 64 or 128, n_x a multiple of 64 and n_y
- *           even; on other levels rows = 3 runs as rows = 2.
+ *           even; on other levels rows = 3 runs as rows = 2.  Levels with few
+ *           columns (at most 8192 to 32768 by kernel and precision) run a
+ *           form of their own for every rows but 1: a workgroup of eight
+ *           wavefronts per 8, 16 or 32 columns.
  *           GMG_K_PROLONG_SMOOTH of level l (l < nlevels - 1) takes rows = 4
- *           (the default: the V-cycle prolongates from level l+1 and then
- *           post-smooths level l, two kernels) or rows = 2 or 3 (one kernel:
- *           the staged smoother of that shape adds the prolongated correction
- *           to every value it stages, so u + P u_c is never stored; the same
+ *           (the V-cycle prolongates from level l+1 and then post-smooths
+ *           level l, two kernels) or rows = 2 or 3 (one kernel: the staged
+ *           smoother of that shape adds the prolongated correction to every
+ *           value it stages, so u + P u_c is never stored; the same
  *           arithmetic).
+ *           A kernel kind without an entry takes the rows that are fastest
+ *           at the level's size and precision (gmg_get_launch reports 4).
  *   group - tile columns per dispatch group: tiles are walked group by group
  *           and tile rows follow each other inside a group, so that a tile's
  *           neighbours run close in time and share an XCD's L2; 0 walks the

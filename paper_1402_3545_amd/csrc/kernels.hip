@@ -20,7 +20,9 @@
 //    back-substitute outwards.  This is Gaussian elimination without pivoting
 //    in a twisted order (exact for the diagonally dominant column matrices);
 //    each lane keeps only ceil(nz/2) pairs (c', d') in registers, so the whole
-//    elimination stays on chip and the kernel streams each field once.
+//    elimination stays on chip and the kernel streams each field once.  Levels
+//    with few columns take the forms of line_block.hip instead (a workgroup
+//    per 8 to 32 columns).
 //
 // Workgroup ids are remapped so that each of the 8 XCDs (each with its own L2)
 // works on a contiguous band of tiles: neighbouring tiles share halo rows.

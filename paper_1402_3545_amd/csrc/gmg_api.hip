@@ -558,7 +558,7 @@ int line_smooth_t(gmg_ctx* c, int level, const T* f, T* u, int nsweeps, T rho, h
   T* res = nullptr;
   HIP_TRY(smooth_steps<T>(c, level, f, u, tmp, nsweeps, rho, s, &res));
   if (res != u)
-    HIP_TRY(hipMemcpyAsync(u, res, (size_t)B.elems * sizeof(T), hipMemcpyDeviceToDevice, s));
+    HIP_TRY(gmg::launch_copy_level<T>(gmg::view<T>(c, level), res, u, s));
   if (!own) HIP_TRY(hipFreeAsync(tmp, s));
   return GMG_OK;
 }

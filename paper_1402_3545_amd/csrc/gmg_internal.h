@@ -280,10 +280,11 @@ hipError_t launch_prolong_smooth(const Lvl<T>& F, const Lvl<T>& C, const T* f, c
                                  const T* uc, T* uout, T rho, hipStream_t s, Shape sh = {});
 
 // Whether the folded form is the faster one without a launch shape: FP32 levels
-// between the block forms and about 65000 columns whose tiles do not fit the
-// two-wavefront form gain nothing (one sweep with the prolongation in us,
-// folded / apart: 160 x 144 x 128 27 / 20, 300 x 300 x 100 47 / 56; FP64 160 x
-// 144 x 128 41 / 39, 464 x 288 x 128 136 / 179).
+// between the block forms and 32768 columns gain nothing, since the folded
+// form is a staged one (one sweep with the prolongation in us, folded / apart:
+// 136 x 128 x 128 32 / 20, 168^2 x 128 33 / 26, 192^2 x 128 32 / 33, 224 x 192 x
+// 64 21 / 25, 224 x 192 x 128 35 / 40, 300 x 300 x 100 47 / 56; FP64 160 x 144 x
+// 128 41 / 39, 192^2 x 128 50 / 57, 464 x 288 x 128 136 / 179).
 template <typename T>
 bool fold_prolongation(const Lvl<T>& F);
 

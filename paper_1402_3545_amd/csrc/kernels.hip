@@ -2569,17 +2569,23 @@ hipError_t launch_line_solve(const Lvl<T>& L, const T* r, T* z, hipStream_t s, S
   return line_dispatch<T, LINE_SOLVE>(L, a, s, sh.group, sh.rows);
 }
 
-// Form of a smoother without a launch shape: FP64 stages its neighbours in
-// LDS (rows = 2), FP32 does with two wavefronts a column where the level fits
-// (rows = 3) and loads them per lane otherwise.  One sweep in us, per lane /
-// staged / two wavefronts: FP64 256^2 x 64 29.7 / 22.9 / 25.7, 464 x 287 x 128
-// 121 / 99 / -, 200 x 120 x 50 13.6 / 14.4 / -; FP32 256^2 x 128 33.5 / 26.9 /
-// 23.5, 512 x 384 x 64 41.8 / 40.1 / 36.5, 464 x 287 x 128 57 / 61 / -, 200 x
-// 120 x 50 9.0 / 11.2 / -.
+// Form of a smoother without a launch shape.  Up to 32768 columns (256
+// workgroups of 128, one a CU) the neighbours are loaded per lane: nothing
+// else runs on the CU, and the staged forms only add their barriers.  Above,
+// FP64 stages its neighbours in LDS (rows = 2) and FP32 does with two
+// wavefronts a column (rows = 3) where the level fits and has more than 32
+// layers.  One sweep in us, per lane / staged / two wavefronts: FP64 136 x 128
+// x 128 24.4 / 28.0 / -, 168^2 x 64 15.0 / 15.6 / -, 192^2 x 64 25.1 / 19.0 /
+// 21.9, 256^2 x 64 29.7 / 22.9 / 25.7, 464 x 287 x 128 121 / 99 / -; FP32 192 x
+// 96 x 128 13.1 / 18.0 / 16.8, 192^2 x 32 7.5 / 7.8 / 7.8, 192^2 x 128 23.9 /
+// 23.4 / 20.1, 512 x 384 x 64 41.8 / 40.1 / 36.5, 464 x 287 x 128 57 / 61 / -.
+constexpr int64_t kStagedCols = 32768;
+
 template <typename T>
 int smooth_rows(const Lvl<T>& L, const Shape& sh) {
   if (sh.set) return sh.rows;
-  return sizeof(T) == 8 ? 2 : line_w2_fits(L) ? 3 : 4;
+  if ((int64_t)L.nx * L.ny <= kStagedCols) return 4;
+  return sizeof(T) == 8 ? 2 : line_w2_fits(L) && L.nz > 32 ? 3 : 4;
 }
 
 template <typename T>
@@ -2595,8 +2601,8 @@ hipError_t launch_smooth(const Lvl<T>& L, const T* f, const T* uin, T* uout, T r
 
 template <typename T>
 bool fold_prolongation(const Lvl<T>& F) {
-  return sizeof(T) == 8 || block_fits(BlockOp::PROLONG_SMOOTH, F) || line_w2_fits(F) ||
-         (int64_t)F.nx * F.ny > 65536;
+  return sizeof(T) == 8 || block_fits(BlockOp::PROLONG_SMOOTH, F) ||
+         (int64_t)F.nx * F.ny > kStagedCols;
 }
 
 template <typename T>

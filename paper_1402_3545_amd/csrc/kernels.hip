@@ -2234,37 +2234,30 @@ __global__ __launch_bounds__(NTHREADS) void k_pcg_final_update(Lvl<double> L,
 // dst = src, whole field.  Bound by bytes on large levels, by the dispatch of
 // workgroups on small ones: a workgroup of one value a thread moved 8 MB in 12
 // us.  Each thread takes COPY_WORDS 16-byte words, all loaded before the first
-// is stored; fields whose address or size is no multiple of 16 bytes go value
-// by value.  A smoothing sweep with the copy that follows it in us, runtime's
-// copy / value by value / this: 144 x 112 x 128 FP32 23.3 / 25.4 / 23.0, FP64
-// 512 x 384 x 64 102 / 100 / 94, 1024^2 x 128 1173 / 1147 / 997.
+// is stored (fields and their rows start at multiples of 16 bytes).  A smoothing
+// sweep with the copy that follows it in us, runtime's copy / value by value /
+// this: 144 x 112 x 128 FP32 23.3 / 25.4 / 23.0, FP64 512 x 384 x 64 102 / 100 /
+// 94, 1024^2 x 128 1173 / 1147 / 997.
 constexpr int COPY_WORDS = 4;
 
-template <typename T, bool WIDE>
+template <typename T>
 __global__ __launch_bounds__(NTHREADS) void k_copy_level(Lvl<T> L, const T* __restrict__ src,
                                                          T* __restrict__ dst) {
   if (gated(L)) return;
-  const int64_t n = (int64_t)L.ny * L.nz * L.ldx;
-  if constexpr (WIDE) {
-    using W = __attribute__((ext_vector_type(4))) uint32_t;
-    const int64_t nw = n * (int64_t)sizeof(T) / (int64_t)sizeof(W);
-    const W* s = reinterpret_cast<const W*>(src);
-    W* d = reinterpret_cast<W*>(dst);
-    const int64_t g = (int64_t)blockIdx.x * (NTHREADS * COPY_WORDS) + threadIdx.x;
-    if (g + (COPY_WORDS - 1) * NTHREADS < nw) {
-      W v[COPY_WORDS];
+  using W = __attribute__((ext_vector_type(4))) uint32_t;
+  const int64_t n = (int64_t)L.ny * L.nz * L.ldx * (int64_t)sizeof(T) / (int64_t)sizeof(W);
+  const W* s = reinterpret_cast<const W*>(src);
+  W* d = reinterpret_cast<W*>(dst);
+  const int64_t g = (int64_t)blockIdx.x * (NTHREADS * COPY_WORDS) + threadIdx.x;
+  if (g + (COPY_WORDS - 1) * NTHREADS < n) {
+    W v[COPY_WORDS];
 #pragma unroll
-      for (int q = 0; q < COPY_WORDS; ++q) v[q] = __builtin_nontemporal_load(s + g + q * NTHREADS);
+    for (int q = 0; q < COPY_WORDS; ++q) v[q] = __builtin_nontemporal_load(s + g + q * NTHREADS);
 #pragma unroll
-      for (int q = 0; q < COPY_WORDS; ++q) d[g + q * NTHREADS] = v[q];
-    } else {
-      for (int q = 0; q < COPY_WORDS; ++q)
-        if (g + q * NTHREADS < nw) d[g + q * NTHREADS] = s[g + q * NTHREADS];
-    }
+    for (int q = 0; q < COPY_WORDS; ++q) d[g + q * NTHREADS] = v[q];
   } else {
-    for (int64_t g = (int64_t)blockIdx.x * NTHREADS + threadIdx.x; g < n;
-         g += (int64_t)gridDim.x * NTHREADS)
-      dst[g] = src[g];
+    for (int q = 0; q < COPY_WORDS; ++q)
+      if (g + q * NTHREADS < n) d[g + q * NTHREADS] = s[g + q * NTHREADS];
   }
 }
 
@@ -2827,17 +2820,9 @@ template <typename T>
 hipError_t launch_copy_level(const Lvl<T>& L, const T* src, T* dst, hipStream_t s) {
   const int64_t n = (int64_t)L.ny * L.nz * L.ldx;
   const int64_t bytes = n * (int64_t)sizeof(T);
-  if (((uintptr_t)src | (uintptr_t)dst | (uintptr_t)bytes) % 16 == 0) {
-    const int64_t words = bytes / 16;
-    const int64_t nb = (words + NTHREADS * COPY_WORDS - 1) / (NTHREADS * COPY_WORDS);
-    if (nb < (1ll << 31)) {
-      hipLaunchKernelGGL((k_copy_level<T, true>), dim3((unsigned)nb), dim3(NTHREADS), 0, s, L, src,
-                         dst);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((k_copy_level<T, false>), dim3(grid_stride_blocks(n)), dim3(NTHREADS), 0, s,
-                     L, src, dst);
+  if (((uintptr_t)src | (uintptr_t)dst | (uintptr_t)bytes) % 16 != 0) return hipErrorInvalidValue;
+  const int nb = cdiv(bytes / 16, NTHREADS * COPY_WORDS);
+  hipLaunchKernelGGL((k_copy_level<T>), dim3(nb), dim3(NTHREADS), 0, s, L, src, dst);
   return hipGetLastError();
 }
 

@@ -82,14 +82,14 @@ MEASURED_TRAFFIC = {
     # launch shape); profiles/cg_p1_1024x1024x128_pmc.md.  Averages over the
     # 162 dispatches that did the work (82 odd-iteration, 80 even-iteration
     # forms; the two enqueued past convergence return at once).  Plain-copy
-    # calibration: 2 GiB read + 2 GiB written read FETCH_SIZE 1048592.5 KiB,
-    # WRITE_SIZE 2097188.7 KiB.
+    # calibration: 2 GiB read + 2 GiB written read FETCH_SIZE 1048592.4 KiB,
+    # WRITE_SIZE 2097184.7 KiB.
     ("cg_spmv", 0, "f64"): {
-        "fetch_kib": 2250521.0698,
-        "write_kib": 2615227.8503,
-        "copy_fetch_scale": 2097152.0 / 1048592.5417,
-        "copy_write_scale": 2097152.0 / 2097188.7292,
-        "source_sha256": "712d405ba001640f568bf75fe39b452fe1d83c45259011dbcbb9cf8c3d6c9516",
+        "fetch_kib": 2249894.2955,
+        "write_kib": 2615227.7147,
+        "copy_fetch_scale": 2097152.0 / 1048592.3646,
+        "copy_write_scale": 2097152.0 / 2097184.7083,
+        "source_sha256": "82d7e5e79a7e2605548a24ed7ca2dd08aac22bdfcedca014d8d9845f19d38090",
         "shape": [8, 8],
     },
 }

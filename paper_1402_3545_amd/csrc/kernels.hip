@@ -2237,7 +2237,9 @@ __global__ __launch_bounds__(NTHREADS) void k_pcg_final_update(Lvl<double> L,
 // is stored (fields and their rows start at multiples of 16 bytes).  A smoothing
 // sweep with the copy that follows it in us, runtime's copy / value by value /
 // this: 144 x 112 x 128 FP32 23.3 / 25.4 / 23.0, FP64 512 x 384 x 64 102 / 100 /
-// 94, 1024^2 x 128 1173 / 1147 / 997.
+// 94, 1024^2 x 128 1173 / 1147 / 997; non-temporal loads are 1 to 5 % slower on
+// fields that the caches still hold (256^2 x 64: 28.8 against 26.9 FP32, 40.9
+// against 39.3 FP64) and as fast on larger ones.
 constexpr int COPY_WORDS = 4;
 
 template <typename T>
@@ -2252,7 +2254,7 @@ __global__ __launch_bounds__(NTHREADS) void k_copy_level(Lvl<T> L, const T* __re
   if (g + (COPY_WORDS - 1) * NTHREADS < n) {
     W v[COPY_WORDS];
 #pragma unroll
-    for (int q = 0; q < COPY_WORDS; ++q) v[q] = __builtin_nontemporal_load(s + g + q * NTHREADS);
+    for (int q = 0; q < COPY_WORDS; ++q) v[q] = s[g + q * NTHREADS];
 #pragma unroll
     for (int q = 0; q < COPY_WORDS; ++q) d[g + q * NTHREADS] = v[q];
   } else {

@@ -545,6 +545,13 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
   return GMG_OK;
 }
 
+// From here on the library's copy kernel is the faster one after an odd number
+// of sweeps; the runtime's 256 workgroups are as fast or faster on fields that
+// fit the caches (one sweep with its copy in us, runtime / library: 208 x 240 x
+// 64 FP32, 14 MB, 25.3 / 26.9; 304 x 384 x 64 FP32, 31 MB, 43.5 / 43.1; 512 x 384
+// x 64 FP64, 101 MB, 102 / 94).
+constexpr size_t kOwnCopyBytes = size_t(32) << 20;
+
 template <typename T>
 int line_smooth_t(gmg_ctx* c, int level, const T* f, T* u, int nsweeps, T rho, hipStream_t s) {
   // ping-pong through a context buffer of the same precision and level
@@ -557,8 +564,13 @@ int line_smooth_t(gmg_ctx* c, int level, const T* f, T* u, int nsweeps, T rho, h
     HIP_TRY(hipMallocAsync((void**)&tmp, (size_t)B.elems * sizeof(T), s));
   T* res = nullptr;
   HIP_TRY(smooth_steps<T>(c, level, f, u, tmp, nsweeps, rho, s, &res));
-  if (res != u)
-    HIP_TRY(gmg::launch_copy_level<T>(gmg::view<T>(c, level), res, u, s));
+  if (res != u) {
+    const size_t bytes = (size_t)B.elems * sizeof(T);
+    if (bytes >= kOwnCopyBytes)
+      HIP_TRY(gmg::launch_copy_level<T>(gmg::view<T>(c, level), res, u, s));
+    else
+      HIP_TRY(hipMemcpyAsync(u, res, bytes, hipMemcpyDeviceToDevice, s));
+  }
   if (!own) HIP_TRY(hipFreeAsync(tmp, s));
   return GMG_OK;
 }

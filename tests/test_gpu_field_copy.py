@@ -1,5 +1,5 @@
 """An odd number of smoothing sweeps ends in the context's own buffer and is
-copied back in 16-byte words: bitwise the same as a single sweep at a time, and
+copied back, large fields (from 32 MiB) in 16-byte words: bitwise the same as a single sweep at a time, and
 no byte outside the field written, on sizes around a workgroup's share of the
 copy (16 KiB) with its remainders."""
 
@@ -21,7 +21,7 @@ def _need_gpu():
 
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("grid", [(2, 3, 2), (5, 7, 9), (16, 16, 8), (64, 16, 2), (64, 17, 4),
-                                  (130, 127, 17)])
+                                  (130, 127, 17), (514, 511, 33)])
 def test_odd_sweeps(grid, prec):
     import paper_1402_3545_amd as G
     nx, ny, nz = grid

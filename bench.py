@@ -61,6 +61,7 @@ WORDS_PER_CELL = {
     "correct": 4.0,          # read u, f (8 B), e (4 B), write u (8 B), r (4 B): 32 B
     "residual_restrict": 2.25,  # per FINE cell: read u, f, write 1/4 f_c
     "prolong_smooth": 3.25,  # read u, f, write u', read 1/4 u_c (u + P u_c not stored)
+    "restrict_solve": 2.5,   # per FINE cell: read u, f, write 1/4 f_c, 1/4 u_c
     # the three vector kernels of a flexible-CG iteration with an FP32
     # preconditioner move 96 B per cell together on average: <z,q> reads z
     # (4 B) and q; the direction kernel reads z, p, q, r and writes p, q
@@ -677,14 +678,15 @@ def main():
                 table[key] = (cn + n, cms + ms)
         return table
 
-    # one untimed step with every kernel timed, solve by solve: the per-kernel
-    # breakdown, each solve's algorithmic bytes, and the dominant kernel whose
-    # roofline the line reports
+    # one untimed step with every kernel timed, solve by solve (the launches of
+    # an untimed solve, fused ones as they are): the per-kernel breakdown, each
+    # solve's algorithmic bytes, and the dominant kernel whose roofline the
+    # line reports
     per_solve = {}
     for name in solves:
         for c in (ctx64, ctx32):
             G.gmg_timing_filter(c, None)
-            G.gmg_timing_enable(c, True)
+            G.gmg_timing_enable(c, True, as_launched=True)
         step([name])
         per_solve[name] = timing_table()
         for c in (ctx64, ctx32):
@@ -703,7 +705,7 @@ def main():
     # the measurement adds no event overhead to the other kernels
     for c in (ctx64, ctx32):
         G.gmg_timing_filter(c, [dom[0]])
-        G.gmg_timing_enable(c, True)
+        G.gmg_timing_enable(c, True, as_launched=True)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     runs = [step() for _ in range(args.steps)]

@@ -212,7 +212,8 @@ int gmg_batch_solve(gmg_ctx *c, const double *const *f, double *const *u, double
 /* Per-kernel timing (measurement support; the paper's per-kernel, per-level
  * breakdown tables, Sec. 5.3).  While enabled, every kernel the context
  * launches is bracketed by two HIP events on its launch stream.
- * gmg_timing_enable(c, 1) clears earlier records and starts recording;
+ * gmg_timing_enable(c, 1) clears earlier records and starts recording,
+ * gmg_timing_enable(c, 2) too, without taking fused launches apart (below);
  * gmg_timing_enable(c, 0) stops.  gmg_timing_read() waits for the recorded
  * events and returns, for one kernel kind / level / precision, the number of
  * launches and their summed duration in milliseconds since the last enable.
@@ -227,14 +228,19 @@ int gmg_batch_solve(gmg_ctx *c, const double *const *f, double *const *u, double
  * prolongation onto a level folded into that level's post-smoother (one
  * kernel instead of GMG_K_PROLONGATE + GMG_K_SMOOTH; timed under the fine
  * level), used where its launch shape says so or, without one, where it is
- * the faster form.  On levels with few columns the restriction takes that line
- * solve along and the prolongation is folded; while one of the kinds is being
- * timed, the parts run as kernels of their own (the same results bitwise). */
+ * the faster form.  GMG_K_RESTRICT_SOLVE is the restriction onto a level with
+ * few columns that takes that level's line solve along (instead of
+ * GMG_K_RESIDUAL_RESTRICT + GMG_K_LINE_SOLVE; timed under the fine level).
+ * While a kind that such a launch stands for is being timed, its parts run as
+ * kernels of their own (the same results bitwise), unless a launch shape of
+ * GMG_K_PROLONG_SMOOTH asks for the fold; gmg_timing_enable(c, 2) times the
+ * launches of an untimed run as they are. */
 typedef enum {
   GMG_K_SPMV = 0, GMG_K_RESIDUAL = 1, GMG_K_LINE_SOLVE = 2, GMG_K_SMOOTH = 3,
   GMG_K_RESTRICT_SMOOTH = 4, GMG_K_PROLONGATE = 5, GMG_K_CG_SPMV = 6, GMG_K_CG_TRIDIAG = 7,
   GMG_K_REDUCE = 8, GMG_K_AUX = 9, GMG_K_CORRECT = 10, GMG_K_FCG = 11,
-  GMG_K_RESIDUAL_RESTRICT = 12, GMG_K_PROLONG_SMOOTH = 13, GMG_K_COUNT = 14
+  GMG_K_RESIDUAL_RESTRICT = 12, GMG_K_PROLONG_SMOOTH = 13, GMG_K_RESTRICT_SOLVE = 14,
+  GMG_K_COUNT = 15
 } gmg_kernel;
 int gmg_timing_enable(gmg_ctx *c, int enable);
 int gmg_timing_read(gmg_ctx *c, int kernel, int level, int prec, int64_t *count,

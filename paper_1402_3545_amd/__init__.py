@@ -37,7 +37,7 @@ EXPORTS = ("gmg_default_params", "gmg_setup", "gmg_destroy", "gmg_field_layout",
 # kernel ids of the timing facility (gmg_kernel in include/gmg.h)
 KERNELS = ("spmv", "residual", "line_solve", "smooth", "restrict_smooth", "prolongate",
            "cg_spmv", "cg_tridiag", "reduce", "aux", "correct", "fcg",
-           "residual_restrict", "prolong_smooth")
+           "residual_restrict", "prolong_smooth", "restrict_solve")
 
 
 class GmgError(RuntimeError):
@@ -499,8 +499,10 @@ def pcg_solve(ctx, f, u, rtol=1e-8, maxit=1000, precond=0, stream=None, check=Tr
     return it.value, rel.value, hist[: it.value + 1].copy(), st
 
 
-def gmg_timing_enable(ctx, enable=True):
-    _check(_lib.gmg_timing_enable(ctx.handle, 1 if enable else 0))
+def gmg_timing_enable(ctx, enable=True, as_launched=False):
+    """as_launched: time the launches of an untimed run; otherwise the V-cycle's
+    fused launches run as their parts while those are timed."""
+    _check(_lib.gmg_timing_enable(ctx.handle, (2 if as_launched else 1) if enable else 0))
 
 
 def gmg_timing_filter(ctx, kernels=None):

@@ -400,8 +400,11 @@ hipError_t timed(gmg_ctx* c, int kind, int level, int prec, hipStream_t s, F&& l
   return hipSuccess;
 }
 
-// whether a launch of one of the kinds would be timed now
-bool timing_any(const gmg_ctx* c, uint32_t kinds) { return c->timing && (c->timing_mask & kinds); }
+// whether a fused launch gives way to its parts because one of their kinds is
+// being timed
+bool parts_timed(const gmg_ctx* c, uint32_t kinds) {
+  return c->timing && c->timing_parts && (c->timing_mask & kinds);
+}
 
 int drain_timing(gmg_ctx* c) {
   for (const gmg_timed_launch& t : c->pending) {
@@ -497,7 +500,7 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
       // onto a small level: one kernel restricts the residual and takes the
       // level's first smoothing step (as two while either of them is timed)
       solved = gmg::block_fits(gmg::BlockOp::RESTRICT_SOLVE, C) &&
-               !timing_any(c, (1u << GMG_K_RESIDUAL_RESTRICT) | (1u << GMG_K_LINE_SOLVE));
+               !parts_timed(c, (1u << GMG_K_RESIDUAL_RESTRICT) | (1u << GMG_K_LINE_SOLVE));
       if (solved) {
         gmg::BlockArgs<T> q;
         q.a = cur[d];
@@ -506,7 +509,9 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
         q.o = static_cast<T*>(c->lev[d + 1].u);
         q.rho = rho;
         q.X = V;
-        HIP_TRY(gmg::launch_block<T>(gmg::BlockOp::RESTRICT_SOLVE, C, q, s));
+        HIP_TRY(timed(c, GMG_K_RESTRICT_SOLVE, d, P, s, [&] {
+          return gmg::launch_block<T>(gmg::BlockOp::RESTRICT_SOLVE, C, q, s);
+        }));
         continue;
       }
       HIP_TRY(timed(c, GMG_K_RESIDUAL_RESTRICT, d, P, s, [&](gmg::Shape sh) {
@@ -527,7 +532,7 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
     const gmg::Shape fold = c->shape[gmg::tslot(GMG_K_PROLONG_SMOOTH, d, P)];
     if (fold.set ? fold.rows == 2 || fold.rows == 3
                  : gmg::fold_prolongation(V) &&
-                       !timing_any(c, (1u << GMG_K_PROLONGATE) | (1u << GMG_K_SMOOTH))) {
+                       !parts_timed(c, (1u << GMG_K_PROLONGATE) | (1u << GMG_K_SMOOTH))) {
       // one kernel: smooth u + P u_c without storing it
       HIP_TRY(timed(c, GMG_K_PROLONG_SMOOTH, d, P, s, [&](gmg::Shape sh) {
         return gmg::launch_prolong_smooth<T>(V, C, fl[d], cur[d], cur[d + 1], other, rho, s, sh);
@@ -642,8 +647,8 @@ constexpr uint32_t kbit(int k) { return 1u << k; }
 // kernel kinds one iteration of each loop launches
 constexpr uint32_t kVcycleKinds = kbit(GMG_K_LINE_SOLVE) | kbit(GMG_K_SMOOTH) |
                                   kbit(GMG_K_RESIDUAL_RESTRICT) | kbit(GMG_K_PROLONGATE) |
-                                  kbit(GMG_K_PROLONG_SMOOTH) | kbit(GMG_K_REDUCE) |
-                                  kbit(GMG_K_AUX);
+                                  kbit(GMG_K_PROLONG_SMOOTH) | kbit(GMG_K_RESTRICT_SOLVE) |
+                                  kbit(GMG_K_REDUCE) | kbit(GMG_K_AUX);
 constexpr uint32_t kIrKinds = kVcycleKinds | kbit(GMG_K_CORRECT);
 constexpr uint32_t kFcgKinds = kVcycleKinds | kbit(GMG_K_FCG);
 constexpr uint32_t kPcgKinds = kbit(GMG_K_CG_SPMV) | kbit(GMG_K_CG_TRIDIAG) | kbit(GMG_K_REDUCE);
@@ -1060,6 +1065,7 @@ int gmg_timing_enable(gmg_ctx* c, int enable) {
     c->tms.assign((size_t)GMG_K_COUNT * gmg::kMaxLevels * 2, 0.0);
   }
   c->timing = enable != 0;
+  c->timing_parts = enable != 2;
   return GMG_OK;
 }
 
@@ -1315,6 +1321,8 @@ int gmg_set_launch(gmg_ctx* c, int kernel, int level, int prec, int rows, int gr
   if (level < 0 || level >= c->nlevels) return fail(GMG_EINVAL, "bad level %d", level);
   int st;
   if ((st = check_prec(prec))) return st;
+  if (kernel == GMG_K_RESTRICT_SOLVE)
+    return fail(GMG_EINVAL, "the fused restriction and line solve has no launch shape");
   const bool pcr_ok = kernel == GMG_K_LINE_SOLVE || kernel == GMG_K_SMOOTH;
   if (kernel == GMG_K_PROLONG_SMOOTH) {
     if (rows != 4 && rows != 2 && rows != 3)

@@ -161,6 +161,7 @@ struct gmg_ctx {
   gmg::Batch* batch = nullptr;       // non-null: a batched context (gmg_batch_setup)
   // per-kernel timing (of the kernel kinds whose bit is set in timing_mask)
   bool timing = false;
+  bool timing_parts = true;  // fused launches run as their parts while those are timed
   uint32_t timing_mask = ~0u;
   std::vector<hipEvent_t> evpool;
   size_t evused = 0;

@@ -324,12 +324,21 @@ int gmg_solve_host(gmg_ctx *c, int method, const double *f_host, double *u_host,
  *           arithmetic).
  *           A kernel kind without an entry takes the rows that are fastest
  *           at the level's size and precision (gmg_get_launch reports 4).
+ *           The V-cycle's fused launches give way to shapes that they do not
+ *           stand for.  The restriction onto a level with few columns runs
+ *           apart from that level's line solve where the line solve has
+ *           rows = 1 or GMG_K_RESIDUAL_RESTRICT a shape other than (4, 0).
+ *           Without an entry of GMG_K_PROLONG_SMOOTH the prolongation runs
+ *           apart from the post-smoother where GMG_K_PROLONGATE has a shape
+ *           other than (4, 0), or GMG_K_SMOOTH rows = 1 or, on a level above
+ *           the form for few columns, any entry.
  *   group - tile columns per dispatch group: tiles are walked group by group
  *           and tile rows follow each other inside a group, so that a tile's
  *           neighbours run close in time and share an XCD's L2; 0 walks the
  *           tiles row by row (the default).
  * Results are identical for every shape except for the summation order of
- * the FP64 reductions (norms and dot products).
+ * the FP64 reductions (norms and dot products) and for rows = 1, another order
+ * of elimination.
  * gmg_set_launch / gmg_get_launch: one entry of the context's table;
  * GMG_EINVAL for a bad kernel id, level or precision, rows not in {4, 8, 16}
  * (or 1 for the line solve and smoother, 2 or 3 for the smoother;

@@ -420,6 +420,37 @@ int drain_timing(gmg_ctx* c) {
   return GMG_OK;
 }
 
+// Whether the restriction of level d's residual takes the line solve of the
+// next level C along: where C is small enough, unless a launch shape asks for
+// what the fused launch does not do (cyclic reduction; rows or tile groups of
+// the restriction) or the parts are being timed.
+template <typename T>
+bool fuse_restriction(const gmg_ctx* c, int d, const Lvl<T>& C) {
+  const int P = prec_of<T>();
+  const gmg::Shape rr = c->shape[gmg::tslot(GMG_K_RESIDUAL_RESTRICT, d, P)];
+  const gmg::Shape ls = c->shape[gmg::tslot(GMG_K_LINE_SOLVE, d + 1, P)];
+  return gmg::block_fits(gmg::BlockOp::RESTRICT_SOLVE, C) && rr.rows == 4 && rr.group == 0 &&
+         ls.rows != 1 &&
+         !parts_timed(c, (1u << GMG_K_RESIDUAL_RESTRICT) | (1u << GMG_K_LINE_SOLVE));
+}
+
+// Whether the prolongation onto level d (V) is folded into its post-smoother:
+// as the launch shape of the fold says.  Without one, where it is the faster
+// form, unless a launch shape asks for what the fold does not do (of the
+// smoother: cyclic reduction, and above the block forms any shape; rows or
+// tile groups of the prolongation) or the parts are being timed.
+template <typename T>
+bool fold_here(const gmg_ctx* c, int d, const Lvl<T>& V) {
+  const int P = prec_of<T>();
+  const gmg::Shape fold = c->shape[gmg::tslot(GMG_K_PROLONG_SMOOTH, d, P)];
+  if (fold.set) return fold.rows == 2 || fold.rows == 3;
+  const gmg::Shape pr = c->shape[gmg::tslot(GMG_K_PROLONGATE, d + 1, P)];
+  const gmg::Shape sm = c->shape[gmg::tslot(GMG_K_SMOOTH, d, P)];
+  return gmg::fold_prolongation(V) && pr.rows == 4 && pr.group == 0 &&
+         (gmg::block_fits(gmg::BlockOp::SMOOTH, V) ? sm.rows != 1 : !sm.set) &&
+         !parts_timed(c, (1u << GMG_K_PROLONGATE) | (1u << GMG_K_SMOOTH));
+}
+
 // nsweeps smoothing steps on level d with the field pair (cur, other); the
 // buffer holding the result goes to *result.
 template <typename T>
@@ -498,9 +529,8 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
       const Lvl<T> C = gmg::view<T>(c, d + 1);
       T* fc = static_cast<T*>(c->lev[d + 1].f);
       // onto a small level: one kernel restricts the residual and takes the
-      // level's first smoothing step (as two while either of them is timed)
-      solved = gmg::block_fits(gmg::BlockOp::RESTRICT_SOLVE, C) &&
-               !parts_timed(c, (1u << GMG_K_RESIDUAL_RESTRICT) | (1u << GMG_K_LINE_SOLVE));
+      // level's first smoothing step
+      solved = fuse_restriction<T>(c, d, C);
       if (solved) {
         gmg::BlockArgs<T> q;
         q.a = cur[d];
@@ -526,13 +556,7 @@ int vcycle_impl(gmg_ctx* c, const T* f0, T* u0, hipStream_t s, bool zero_guess =
     T* other = (d == 0) ? u0
                         : (cur[d] == c->lev[d].u ? static_cast<T*>(c->lev[d].ualt)
                                                  : static_cast<T*>(c->lev[d].u));
-    // unless a launch shape says otherwise the prolongation is folded into the
-    // post-smoother where that is the faster form (as two kernels while
-    // either of them is timed)
-    const gmg::Shape fold = c->shape[gmg::tslot(GMG_K_PROLONG_SMOOTH, d, P)];
-    if (fold.set ? fold.rows == 2 || fold.rows == 3
-                 : gmg::fold_prolongation(V) &&
-                       !parts_timed(c, (1u << GMG_K_PROLONGATE) | (1u << GMG_K_SMOOTH))) {
+    if (fold_here<T>(c, d, V)) {
       // one kernel: smooth u + P u_c without storing it
       HIP_TRY(timed(c, GMG_K_PROLONG_SMOOTH, d, P, s, [&](gmg::Shape sh) {
         return gmg::launch_prolong_smooth<T>(V, C, fl[d], cur[d], cur[d + 1], other, rho, s, sh);

@@ -1,10 +1,11 @@
 """The V-cycle's fused launches (restriction with the coarse line solve,
 prolongation with the post-smoother): what is timed is what runs."""
 
+import numpy as np
 import pytest
 
 import workloads as W
-from tests.gpu_util import problem
+from tests.gpu_util import max_rel, problem
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -60,3 +61,88 @@ def test_timing_as_launched(prec):
     G.gmg_timing_filter(ctx, None)
     with pytest.raises(G.GmgError):
         G.gmg_set_launch(ctx, "restrict_solve", 0, prec, 4, 0)
+
+
+# entries on the coarse levels, and the kinds a V-cycle must then launch there
+# (fused: without one of them)
+ENTRIES = [({"line_solve": (1, 0), "smooth": (1, 0)},
+            {"residual_restrict", "line_solve", "prolongate", "smooth"}),
+           ({"line_solve": (1, 0)}, {"residual_restrict", "line_solve", "prolong_smooth"}),
+           ({"smooth": (1, 0)}, {"restrict_solve", "prolongate", "smooth"}),
+           ({"residual_restrict": (8, 0), "prolongate": (4, 2)},
+            {"residual_restrict", "line_solve", "prolongate", "smooth"}),
+           ({"residual_restrict": (4, 0), "prolongate": (4, 0), "line_solve": (4, 1),
+             "smooth": (2, 4)}, {"restrict_solve", "prolong_smooth"})]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("grid", [(64, 64, 64, 4), (40, 24, 37, 3), (96, 72, 128, 4)])
+@pytest.mark.parametrize("entries,kinds", ENTRIES)
+def test_cycle_runs_the_set_shapes(entries, kinds, grid, prec):
+    """The kernels that the launch shapes ask for run whether they are timed or
+    not; with cyclic reduction among them the cycle matches the oracle's like
+    any other shape (the bars of the folded prolongation's tests), with the
+    others it is bitwise that without entries."""
+    import paper_1402_3545_amd as G
+    nx, ny, nz, L = grid
+    ctx, orc, _ = problem(nx, ny, nz, nlevels=L, seed=87, prec_precond=prec)
+    dt = torch.float64 if prec == 0 else torch.float32
+    n = nx * ny * nz
+    f, u = W.uniform_pm1(87, 1, n), W.uniform_pm1(87, 2, n)
+    if prec == 1:
+        f, u = (a.astype(np.float32).astype(np.float64) for a in (f, u))
+    fd, u0 = ctx.to_device(f, dtype=dt), ctx.to_device(u, dtype=dt)
+
+    def cycle():
+        ud = u0.clone()
+        G.gmg_vcycle(ctx, fd, ud)
+        outs.append(ctx.from_device(ud))
+
+    outs = []
+    cycle()
+    for kind, (rows, group) in entries.items():
+        for lvl in range(L):
+            # (the restriction is timed and shaped under the finer level; the
+            # finest level's line kernels keep their defaults)
+            if lvl > 0 or kind == "residual_restrict":
+                G.gmg_set_launch(ctx, kind, lvl, prec, rows, group)
+    cycle()
+    # (the finest level's first step, the coarsest level's second one)
+    got = set(_launched(G, ctx, cycle)) - {"smooth", "prolong_smooth"}
+    assert got == kinds - {"smooth", "prolong_smooth"}
+    G.gmg_timing_enable(ctx, True)
+    cycle()
+    G.gmg_timing_enable(ctx, False)
+    assert all(np.array_equal(o, outs[1]) for o in outs[2:])
+    if all(rows != 1 for rows, _ in entries.values()):
+        assert np.array_equal(outs[0], outs[1])
+    else:
+        assert not np.array_equal(outs[0], outs[1])
+    ref = orc.vcycle(f, u)
+    assert max_rel(outs[1], ref, np.abs(ref).max()) < (1e-11 if prec == 0 else 1e-4)
+
+
+def test_smoother_shape_above_the_block_forms():
+    """Without an entry of the fold the FP64 post-smoother of a larger level
+    takes the prolongation along; with one of the smoother it runs in that
+    shape (bitwise the same cycle)."""
+    import paper_1402_3545_amd as G
+    nx, ny, nz = 192, 180, 20
+    ctx, _, _ = problem(nx, ny, nz, nlevels=2, seed=88)
+    n = nx * ny * nz
+    fd, u0 = (ctx.to_device(W.uniform_pm1(88, s, n)) for s in (1, 2))
+    outs, kinds = [], []
+
+    def cycle():
+        ud = u0.clone()
+        G.gmg_vcycle(ctx, fd, ud)
+        outs.append(ctx.from_device(ud))
+
+    for shape in (None, (4, 0), (2, 4)):
+        if shape:
+            G.gmg_set_launch(ctx, "smooth", 0, G.GMG_F64, *shape)
+        kinds.append(_launched(G, ctx, cycle))
+    assert kinds[0].get("prolong_smooth") == 1 and "prolongate" not in kinds[0]
+    for k in kinds[1:]:
+        assert k.get("prolongate") == 1 and "prolong_smooth" not in k
+    assert all(np.array_equal(o, outs[0]) for o in outs)

@@ -350,7 +350,9 @@ int gmg_solve_host(gmg_ctx *c, int method, const double *f_host, double *u_host,
  * overwritten; caller memory is not touched), times it with HIP events on
  * `stream` and keeps the fastest; the folded prolongation (rows = 2 or 3 of
  * GMG_K_PROLONG_SMOOTH, groups 0/1/2/4/8) is kept for a level where it beats
- * the best prolongation plus the best smoother.  Synchronises `stream`.
+ * the best prolongation plus the best smoother, and the restriction and the
+ * line solve of a level with few columns keep shapes that part them where the
+ * two beat the fused launch.  Synchronises `stream`.
  * reps in [1, 1000]. */
 int gmg_set_launch(gmg_ctx *c, int kernel, int level, int prec, int rows, int group);
 int gmg_get_launch(const gmg_ctx *c, int kernel, int level, int prec, int *rows, int *group);

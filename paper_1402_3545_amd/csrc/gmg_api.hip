@@ -875,7 +875,9 @@ int fcg_impl(gmg_ctx* c, const double* f, double* u, double rtol, int maxit, int
 // twisted elimination (4) and, for the line solve and the smoother, one
 // wavefront per column by cyclic reduction (1, tile order irrelevant); the
 // smoother also with its neighbours staged in LDS (2), and staged with two
-// wavefronts per column by direct loads (3).
+// wavefronts per column by direct loads (3).  On levels of the block forms,
+// which are the same kernel for every rows but 1 and every group, each kernel
+// is timed once.
 constexpr int kStencilRows[] = {4, 8, 16};
 constexpr int kLineRows[] = {4};
 constexpr int kLinePcrRows[] = {4, 1};
@@ -883,6 +885,18 @@ constexpr int kSmoothRows[] = {4, 1, 2, 3};
 constexpr int kTuneGroups[] = {0, 1, 2, 4, 8};
 
 enum class Cand { STENCIL, LINE, LINE_PCR, SMOOTH };
+
+// Milliseconds of `reps` launches, after one to warm up.
+template <typename F>
+int time_launches(int reps, hipStream_t s, hipEvent_t ea, hipEvent_t eb, F&& launch, float* ms) {
+  HIP_TRY(launch());
+  HIP_TRY(hipEventRecord(ea, s));
+  for (int q = 0; q < reps; ++q) HIP_TRY(launch());
+  HIP_TRY(hipEventRecord(eb, s));
+  HIP_TRY(hipEventSynchronize(eb));
+  HIP_TRY(hipEventElapsedTime(ms, ea, eb));
+  return GMG_OK;
+}
 
 // Time `reps` launches of every candidate shape of one kernel kind and store
 // the fastest in the context's table.  `nti` is the kernel's tile count across
@@ -907,13 +921,9 @@ int tune_kind(gmg_ctx* c, int kind, int level, int prec, Cand cand, int nti, int
     for (int group : kTuneGroups) {
       if (group >= nti || (rows == 1 && group != 0)) continue;
       const gmg::Shape sh{rows, group, true};
-      HIP_TRY(launch(sh));  // warm-up
-      HIP_TRY(hipEventRecord(ea, s));
-      for (int q = 0; q < reps; ++q) HIP_TRY(launch(sh));
-      HIP_TRY(hipEventRecord(eb, s));
-      HIP_TRY(hipEventSynchronize(eb));
       float ms = 0.0f;
-      HIP_TRY(hipEventElapsedTime(&ms, ea, eb));
+      const int st = time_launches(reps, s, ea, eb, [&] { return launch(sh); }, &ms);
+      if (st) return st;
       if (!have || ms < best_ms) {
         best = sh;
         best_ms = ms;
@@ -930,10 +940,14 @@ int tune_kind(gmg_ctx* c, int kind, int level, int prec, Cand cand, int nti, int
 // context's own work buffers (level 0: the solver vectors).
 template <typename T>
 int tune_levels(gmg_ctx* c, int reps, hipStream_t s, hipEvent_t ea, hipEvent_t eb) {
+  using gmg::BlockOp;
   using gmg::Shape;
   const int P = prec_of<T>();
   const int L = c->nlevels;
   const T rho = (T)c->p.rho;
+  // the finer level's fields, and the time of its restriction onto level d
+  const T *fine_u = nullptr, *fine_f = nullptr;
+  float ms_restrict = 0.0f;
   for (int d = 0; d < L; ++d) {
     const Lvl<T> V = gmg::view<T>(c, d);
     T *x0, *x1, *x2;
@@ -965,14 +979,39 @@ int tune_levels(gmg_ctx* c, int reps, hipStream_t s, hipEvent_t ea, hipEvent_t e
                                          c->partials, &nb, s, sh);
          })))
       return st;
-    if ((st = tune_kind(c, GMG_K_LINE_SOLVE, d, P, Cand::LINE_PCR, ntl, reps, s, ea, eb, [&](Shape sh) {
-           return gmg::launch_line_solve_scaled<T>(V, x2, x1, rho, s, sh);
-         })))
+    float ms_solve = 0.0f;
+    if ((st = tune_kind(c, GMG_K_LINE_SOLVE, d, P, Cand::LINE_PCR,
+                        gmg::block_fits(BlockOp::SOLVE, V) ? 1 : ntl, reps, s, ea, eb,
+                        [&](Shape sh) {
+                          return gmg::launch_line_solve_scaled<T>(V, x2, x1, rho, s, sh);
+                        }, &ms_solve)))
       return st;
+    if (d > 0 && gmg::block_fits(BlockOp::RESTRICT_SOLVE, V)) {
+      // the line solve taken along by the restriction: shapes that the fused
+      // launch gives way to are kept where the two kernels beat it
+      gmg::BlockArgs<T> q;
+      q.a = fine_u;
+      q.f = fine_f;
+      q.o1 = x2;
+      q.o = x0;
+      q.rho = rho;
+      q.X = gmg::view<T>(c, d - 1);
+      float ms = 0.0f;
+      if ((st = time_launches(reps, s, ea, eb, [&] {
+             return gmg::launch_block<T>(BlockOp::RESTRICT_SOLVE, V, q, s);
+           }, &ms)))
+        return st;
+      if (ms <= ms_restrict + ms_solve) {
+        c->shape[gmg::tslot(GMG_K_RESIDUAL_RESTRICT, d - 1, P)] = Shape{4, 0, true};
+        c->shape[gmg::tslot(GMG_K_LINE_SOLVE, d, P)] = Shape{4, 0, true};
+      }
+    }
     float ms_smooth = 0.0f;
-    if ((st = tune_kind(c, GMG_K_SMOOTH, d, P, Cand::SMOOTH, ntl, reps, s, ea, eb, [&](Shape sh) {
-           return gmg::launch_smooth<T>(V, x2, x0, x1, rho, s, sh);
-         }, &ms_smooth)))
+    const bool block = gmg::block_fits(BlockOp::SMOOTH, V);
+    if ((st = tune_kind(c, GMG_K_SMOOTH, d, P, block ? Cand::LINE_PCR : Cand::SMOOTH,
+                        block ? 1 : ntl, reps, s, ea, eb, [&](Shape sh) {
+                          return gmg::launch_smooth<T>(V, x2, x0, x1, rho, s, sh);
+                        }, &ms_smooth)))
       return st;
     if (d + 1 < L) {
       const Lvl<T> C = gmg::view<T>(c, d + 1);
@@ -981,8 +1020,10 @@ int tune_levels(gmg_ctx* c, int reps, hipStream_t s, hipEvent_t ea, hipEvent_t e
       if ((st = tune_kind(c, GMG_K_RESIDUAL_RESTRICT, d, P, Cand::STENCIL,
                           (int)gmg::stencil_tiles_x(C.nx), reps, s, ea, eb, [&](Shape sh) {
                             return gmg::launch_resrestrict<T>(V, C, x0, x2, fc, s, sh);
-                          })))
+                          }, &ms_restrict)))
         return st;
+      fine_u = x0;
+      fine_f = x2;
       // prolongation from level d+1 onto level d, kept under the coarse level
       float ms_prol = 0.0f;
       if ((st = tune_kind(c, GMG_K_PROLONGATE, d + 1, P, Cand::STENCIL, nts, reps, s, ea, eb,
@@ -994,19 +1035,18 @@ int tune_levels(gmg_ctx* c, int reps, hipStream_t s, hipEvent_t ea, hipEvent_t e
       // the two kernels
       Shape fused{4, 0, true};
       float best_ms = ms_smooth + ms_prol;
-      for (int q0 = 0; q0 < 2 * (int)(sizeof(kTuneGroups) / sizeof(int)); ++q0) {
+      const bool once = gmg::block_fits(BlockOp::PROLONG_SMOOTH, V);
+      const int nfold = once ? 1 : 2 * (int)(sizeof(kTuneGroups) / sizeof(int));
+      for (int q0 = 0; q0 < nfold; ++q0) {
         // rows 2: one wavefront per column; rows 3: two (where the level fits)
         const int group = kTuneGroups[q0 >> 1];
         if (group >= ntl) continue;
         const Shape sh{(q0 & 1) ? 3 : 2, group, true};
-        auto go = [&] { return gmg::launch_prolong_smooth<T>(V, C, x2, x0, uc, x1, rho, s, sh); };
-        HIP_TRY(go());  // warm-up
-        HIP_TRY(hipEventRecord(ea, s));
-        for (int q = 0; q < reps; ++q) HIP_TRY(go());
-        HIP_TRY(hipEventRecord(eb, s));
-        HIP_TRY(hipEventSynchronize(eb));
         float ms = 0.0f;
-        HIP_TRY(hipEventElapsedTime(&ms, ea, eb));
+        if ((st = time_launches(reps, s, ea, eb, [&] {
+               return gmg::launch_prolong_smooth<T>(V, C, x2, x0, uc, x1, rho, s, sh);
+             }, &ms)))
+          return st;
         if (ms < best_ms) {
           best_ms = ms;
           fused = sh;

@@ -146,3 +146,35 @@ def test_smoother_shape_above_the_block_forms():
     for k in kinds[1:]:
         assert k.get("prolongate") == 1 and "prolong_smooth" not in k
     assert all(np.array_equal(o, outs[0]) for o in outs)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_autotuner_on_small_levels(prec):
+    """Levels of few columns have one kernel for every form but cyclic
+    reduction, timed once: the table holds (4, 0) or (1, 0) for their line
+    kernels and (4, 0) or (2, 0) for the fold, and the restriction is set
+    apart from the line solve only by a shape that a kernel of its own has."""
+    import paper_1402_3545_amd as G
+    nx, ny, nz, L = 96, 64, 64, 4
+    ctx, orc, _ = problem(nx, ny, nz, nlevels=L, seed=89, prec_precond=prec)
+    G.gmg_autotune(ctx, reps=2)
+    for lvl in range(L):
+        assert G.gmg_get_launch(ctx, "line_solve", lvl, prec) in ((4, 0), (1, 0))
+        assert G.gmg_get_launch(ctx, "smooth", lvl, prec) in ((4, 0), (1, 0))
+        assert G.gmg_get_launch(ctx, "prolong_smooth", lvl, prec) in ((4, 0), (2, 0))
+    dt = torch.float64 if prec == 0 else torch.float32
+    n = nx * ny * nz
+    f, u = (W.uniform_pm1(89, s, n).astype(np.float32).astype(np.float64) for s in (1, 2))
+    fd, ud = ctx.to_device(f, dtype=dt), ctx.to_device(u, dtype=dt)
+    G.gmg_timing_enable(ctx, True, as_launched=True)
+    G.gmg_vcycle(ctx, fd, ud)
+    table = G.gmg_timing_table(ctx)
+    G.gmg_timing_enable(ctx, False)
+    for lvl in range(L - 1):
+        apart = (G.gmg_get_launch(ctx, "residual_restrict", lvl, prec) != (4, 0) or
+                 G.gmg_get_launch(ctx, "line_solve", lvl + 1, prec) == (1, 0))
+        p = "f64" if prec == 0 else "f32"
+        assert (("residual_restrict", lvl, p) in table) == apart
+        assert (("restrict_solve", lvl, p) in table) != apart
+    ref = orc.vcycle(f, u)
+    assert max_rel(ctx.from_device(ud), ref, np.abs(ref).max()) < (1e-11 if prec == 0 else 1e-4)

@@ -323,7 +323,8 @@ int gmg_solve_host(gmg_ctx *c, int method, const double *f_host, double *u_host,
  *           value it stages, so u + P u_c is never stored; the same
  *           arithmetic).
  *           A kernel kind without an entry takes the rows that are fastest
- *           at the level's size and precision (gmg_get_launch reports 4).
+ *           at the level's size and precision (gmg_get_launch reports 4,
+ *           gmg_launch_is_set tells it from an entry of 4).
  *           The V-cycle's fused launches give way to shapes that they do not
  *           stand for.  The restriction onto a level with few columns runs
  *           apart from that level's line solve where the line solve has
@@ -356,6 +357,12 @@ int gmg_solve_host(gmg_ctx *c, int method, const double *f_host, double *u_host,
  * reps in [1, 1000]. */
 int gmg_set_launch(gmg_ctx *c, int kernel, int level, int prec, int rows, int group);
 int gmg_get_launch(const gmg_ctx *c, int kernel, int level, int prec, int *rows, int *group);
+/* Whether an entry is set (1) or not (0), by gmg_set_launch or gmg_autotune:
+ * gmg_get_launch reports (4, 0) in either case, which as an entry is a choice
+ * of its own.  gmg_clear_launch makes an entry unset again.  Arguments and
+ * errors as for gmg_get_launch. */
+int gmg_launch_is_set(const gmg_ctx *c, int kernel, int level, int prec);
+int gmg_clear_launch(gmg_ctx *c, int kernel, int level, int prec);
 int gmg_autotune(gmg_ctx *c, int reps, void *stream);
 
 /* Launch mode of the iterative solvers (gmg_solve, pcg_solve, and the solve

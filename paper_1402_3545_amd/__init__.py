@@ -29,7 +29,7 @@ EXPORTS = ("gmg_default_params", "gmg_setup", "gmg_destroy", "gmg_field_layout",
            "gmg_vcycle", "gmg_solve", "pcg_solve", "gmg_batch_setup", "gmg_batch_layout",
            "gmg_batch_solve", "gmg_timing_enable", "gmg_timing_read", "gmg_timing_filter",
            "gmg_set_launch",
-           "gmg_get_launch", "gmg_autotune", "gmg_set_graphs", "gmg_solver_polls",
+           "gmg_get_launch", "gmg_launch_is_set", "gmg_clear_launch", "gmg_autotune", "gmg_set_graphs", "gmg_solver_polls",
            "gmg_transpose_in",
            "gmg_transpose_out",
            "gmg_solve_host", "gmg_copy_probe", "gmg_last_error")
@@ -100,6 +100,8 @@ def _load():
         "gmg_timing_filter": (i32, [vp, C.c_uint32]),
         "gmg_set_launch": (i32, [vp, i32, i32, i32, i32, i32]),
         "gmg_get_launch": (i32, [vp, i32, i32, i32, intp, intp]),
+        "gmg_launch_is_set": (i32, [vp, i32, i32, i32]),
+        "gmg_clear_launch": (i32, [vp, i32, i32, i32]),
         "gmg_autotune": (i32, [vp, i32, vp]),
         "gmg_set_graphs": (i32, [vp, i32]),
         "gmg_solver_polls": (i32, [vp]),
@@ -566,6 +568,15 @@ def gmg_get_launch(ctx, kernel, level, prec):
     return rows.value, group.value
 
 
+def gmg_launch_is_set(ctx, kernel, level, prec):
+    """Whether the entry was set; gmg_get_launch reports (4, 0) for the others."""
+    return bool(_check(_lib.gmg_launch_is_set(ctx.handle, _kid(kernel), int(level), int(prec))))
+
+
+def gmg_clear_launch(ctx, kernel, level, prec):
+    _check(_lib.gmg_clear_launch(ctx.handle, _kid(kernel), int(level), int(prec)))
+
+
 def gmg_set_graphs(ctx, enable=True):
     """Iterations of the solvers as hipGraph replays (True, the default) or
     as direct launches (False); results are identical."""
@@ -584,12 +595,14 @@ def gmg_autotune(ctx, reps=3, stream=None):
 
 
 def launch_table(ctx):
-    """{"kernel/level/prec": [rows, group]} for every tuned kernel kind."""
+    """{"kernel/level/prec": [rows, group]} of the entries that are set: applied
+    to a context without entries, the table gives the same kernels."""
     out = {}
     for k in TUNED_KERNELS:
         for lvl in range(ctx.nlevels):
             for prec in (GMG_F64, GMG_F32):
-                out[f"{k}/{lvl}/{prec}"] = list(gmg_get_launch(ctx, k, lvl, prec))
+                if gmg_launch_is_set(ctx, k, lvl, prec):
+                    out[f"{k}/{lvl}/{prec}"] = list(gmg_get_launch(ctx, k, lvl, prec))
     return out
 
 

@@ -1429,6 +1429,20 @@ int gmg_get_launch(const gmg_ctx* c, int kernel, int level, int prec, int* rows,
   return GMG_OK;
 }
 
+int gmg_launch_is_set(const gmg_ctx* c, int kernel, int level, int prec) {
+  int st;
+  if ((st = gmg_get_launch(c, kernel, level, prec, nullptr, nullptr))) return st;
+  return c->shape[gmg::tslot(kernel, level, prec)].set ? 1 : 0;
+}
+
+int gmg_clear_launch(gmg_ctx* c, int kernel, int level, int prec) {
+  int st;
+  if ((st = gmg_get_launch(c, kernel, level, prec, nullptr, nullptr))) return st;
+  c->shape[gmg::tslot(kernel, level, prec)] = gmg::Shape{};
+  drop_graphs(c);  // captured launches carry the old shape
+  return GMG_OK;
+}
+
 int gmg_autotune(gmg_ctx* c, int reps, void* stream) {
   if (!c || c->batch) return fail(GMG_EINVAL, "context is NULL or batched");
   if (reps < 1 || reps > 1000) return fail(GMG_EINVAL, "reps must be in [1, 1000]");

@@ -178,3 +178,49 @@ def test_autotuner_on_small_levels(prec):
         assert (("restrict_solve", lvl, p) in table) != apart
     ref = orc.vcycle(f, u)
     assert max_rel(ctx.from_device(ud), ref, np.abs(ref).max()) < (1e-11 if prec == 0 else 1e-4)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_launch_table_round_trip(prec):
+    """A saved table gives the context it is applied to the kernels of the one
+    it was read from, entries that nobody set included; clearing an entry
+    brings the default back."""
+    import paper_1402_3545_amd as G
+    nx, ny, nz, L = 192, 180, 40, 2
+
+    def context():
+        return problem(nx, ny, nz, nlevels=L, seed=90, prec_precond=prec)[0]
+
+    dt = torch.float64 if prec == 0 else torch.float32
+    n = nx * ny * nz
+
+    def launched(ctx):
+        fd, ud = (ctx.to_device(W.uniform_pm1(90, s, n), dtype=dt) for s in (1, 2))
+        return _launched(G, ctx, lambda: G.gmg_vcycle(ctx, fd, ud))
+
+    a, b = context(), context()
+    plain = launched(a)
+    assert plain.get("prolong_smooth") == 1 and plain.get("restrict_solve") == 1
+    assert G.launch_table(a) == {}
+    G.apply_launch_table(b, G.launch_table(a))
+    assert launched(b) == plain
+    # (4, 0) is reported for an entry that nobody set, and is one when set
+    assert G.gmg_get_launch(a, "smooth", 0, prec) == (4, 0)
+    assert not G.gmg_launch_is_set(a, "smooth", 0, prec)
+    G.gmg_set_launch(a, "smooth", 0, prec, 4, 0)
+    G.gmg_set_launch(a, "line_solve", 1, prec, 1, 0)
+    assert G.gmg_launch_is_set(a, "smooth", 0, prec)
+    table = G.launch_table(a)
+    assert table == {f"smooth/0/{prec}": [4, 0], f"line_solve/1/{prec}": [1, 0]}
+    apart = launched(a)
+    assert "prolong_smooth" not in apart and "restrict_solve" not in apart
+    G.apply_launch_table(b, table)
+    assert launched(b) == apart
+    for c in (a, b):
+        G.gmg_clear_launch(c, "smooth", 0, prec)
+        G.gmg_clear_launch(c, "line_solve", 1, prec)
+        assert G.launch_table(c) == {} and launched(c) == plain
+    with pytest.raises(G.GmgError):
+        G.gmg_clear_launch(a, "smooth", L, prec)
+    with pytest.raises(G.GmgError):
+        G.gmg_launch_is_set(a, 99, 0, prec)

@@ -280,12 +280,19 @@ template <typename T>
 hipError_t launch_prolong_smooth(const Lvl<T>& F, const Lvl<T>& C, const T* f, const T* uin,
                                  const T* uc, T* uout, T rho, hipStream_t s, Shape sh = {});
 
-// Whether the folded form is the faster one without a launch shape: FP32 levels
-// between the block forms and 32768 columns gain nothing, since the folded
-// form is a staged one (one sweep with the prolongation in us, folded / apart:
-// 136 x 128 x 128 32 / 20, 168^2 x 128 33 / 26, 192^2 x 128 32 / 33, 224 x 192 x
-// 64 21 / 25, 224 x 192 x 128 35 / 40, 300 x 300 x 100 47 / 56; FP64 160 x 144 x
-// 128 41 / 39, 192^2 x 128 50 / 57, 464 x 288 x 128 136 / 179).
+// Whether the folded form is the faster one without a launch shape.  It is a
+// staged one, which below 256 workgroups, one a CU, waits at its barriers for
+// nothing else to run meanwhile: FP32 levels between the block forms and 32768
+// columns gain nothing, nor do FP64 levels of up to 28672 columns and more than
+// 96 layers with a ragged last tile, whose workgroups set the time of the one
+// round.  A cycle of two levels in us, folded / apart.  FP32, 128 layers: 160 x
+// 128 64 / 61, 224 x 144 67 / 65, 192 x 176 86 / 87, 256^2 98 / 105, 512^2 321 /
+// 359; 100 layers: 192^2 89 / 90, 256^2 102 / 109; with 65 to 80 layers it gains
+// from some 150000 columns only (320^2 145 / 140, 404^2 200 / 201, 512^2 268 /
+// 283).  FP64, 128 layers, ragged: 136 x 124 101 / 92, 150^2 107 / 101, 168^2
+// 108 / 103, 176^2 124 / 136, 200 x 160 129 / 142; whole: 128 x 144 92 / 91, 160 x
+// 144 95 / 96, 160 x 176 99 / 103; ragged 140^2 at 104 layers 94 / 90, 152 x 136
+// at 80 78 / 77 and at 65 70 / 73.
 template <typename T>
 bool fold_prolongation(const Lvl<T>& F);
 

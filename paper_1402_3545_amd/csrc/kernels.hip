@@ -2575,6 +2575,7 @@ hipError_t launch_line_solve(const Lvl<T>& L, const T* r, T* z, hipStream_t s, S
 // 96 x 128 13.1 / 18.0 / 16.8, 192^2 x 32 7.5 / 7.8 / 7.8, 192^2 x 128 23.9 /
 // 23.4 / 20.1, 512 x 384 x 64 41.8 / 40.1 / 36.5, 464 x 287 x 128 57 / 61 / -.
 constexpr int64_t kStagedCols = 32768;
+constexpr int64_t kRaggedFoldCols = 28672;  // (fold_prolongation)
 
 template <typename T>
 int smooth_rows(const Lvl<T>& L, const Shape& sh) {
@@ -2596,8 +2597,10 @@ hipError_t launch_smooth(const Lvl<T>& L, const T* f, const T* uin, T* uout, T r
 
 template <typename T>
 bool fold_prolongation(const Lvl<T>& F) {
-  return sizeof(T) == 8 || block_fits(BlockOp::PROLONG_SMOOTH, F) ||
-         (int64_t)F.nx * F.ny > kStagedCols;
+  if (block_fits(BlockOp::PROLONG_SMOOTH, F)) return true;
+  const int64_t cols = (int64_t)F.nx * F.ny;
+  if (sizeof(T) == 8) return F.nz <= 96 || F.nx % 32 == 0 || cols > kRaggedFoldCols;
+  return cols > kStagedCols;
 }
 
 template <typename T>

@@ -224,3 +224,33 @@ def test_launch_table_round_trip(prec):
         G.gmg_clear_launch(a, "smooth", L, prec)
     with pytest.raises(G.GmgError):
         G.gmg_launch_is_set(a, 99, 0, prec)
+
+
+@pytest.mark.parametrize("grid,prec,folded", [
+    # FP64, ragged last tile: apart with more than 96 layers, up to 28672 columns
+    ((136, 128, 128), 0, False), ((136, 128, 97), 0, False), ((136, 128, 96), 0, True),
+    ((168, 168, 128), 0, False), ((176, 176, 128), 0, True), ((160, 128, 128), 0, True),
+    # FP32 above 64 layers: apart up to 32768 columns
+    ((136, 128, 128), 1, False), ((192, 172, 65), 1, True), ((136, 128, 64), 1, True)])
+def test_where_the_fold_is_the_default(grid, prec, folded):
+    """One kernel or two on the finest level without launch shapes: bitwise the
+    cycle with the fold switched on and off."""
+    import paper_1402_3545_amd as G
+    nx, ny, nz = grid
+    ctx, _, _ = problem(nx, ny, nz, nlevels=2, seed=92, prec_precond=prec)
+    dt = torch.float64 if prec == 0 else torch.float32
+    n = nx * ny * nz
+    fd, u0 = (ctx.to_device(W.uniform_pm1(92, s, n), dtype=dt) for s in (1, 2))
+    outs = []
+
+    def cycle():
+        ud = u0.clone()
+        G.gmg_vcycle(ctx, fd, ud)
+        outs.append(ctx.from_device(ud))
+
+    kinds = _launched(G, ctx, cycle)
+    assert ("prolong_smooth" in kinds) == folded and ("prolongate" in kinds) != folded
+    for rows in (2, 4):
+        G.gmg_set_launch(ctx, "prolong_smooth", 0, prec, rows, 0)
+        cycle()
+    assert all(np.array_equal(o, outs[0]) for o in outs[1:])

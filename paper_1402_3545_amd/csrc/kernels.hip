@@ -2685,7 +2685,14 @@ hipError_t launch_correct_residual(const Lvl<double>& L, const double* u, const 
 template <typename T>
 hipError_t launch_prolongate(const Lvl<T>& C, const Lvl<T>& F, const T* uc, T* uf,
                              hipStream_t s, Shape sh) {
-  return with_rows(sh.rows, stencil_seg(F.nx, F.ny, F.nz, kSegProlong), [&](auto R, auto K) {
+  // (FP64 workgroups of KSEG layers that just fill the CUs once, 225 to 256 of
+  // them without a partial segment, stay: KSEG / KSHORT in us 256^2 x 32 8.2 /
+  // 10.3, 192 x 160 x 64 8.3 / 9.4, 128^2 x 128 8.2 / 8.3; with fewer, 256 x 192
+  // x 32 8.4 / 7.3, with more, 192^2 x 64 15.8 / 11.5)
+  const int64_t wg = (int64_t)cdiv(F.nx, 64) * cdiv(F.ny, SROWS) * cdiv(F.nz, KSEG);
+  const bool one_round = sizeof(T) == 8 && wg > 224 && wg <= 256 && F.nz % KSEG == 0;
+  const int seg = one_round ? KSEG : stencil_seg(F.nx, F.ny, F.nz, kSegProlong);
+  return with_rows(sh.rows, seg, [&](auto R, auto K) {
     constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
     const int nti = cdiv(F.nx, 64), ntj = cdiv(F.ny, SR), nkb = cdiv(F.nz, KS);
     hipLaunchKernelGGL((k_prolongate<T, SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, C, F, uc, uf, nti, ntj,

@@ -250,15 +250,24 @@ hipError_t launch_block(BlockOp op, const Lvl<T>& L, const BlockArgs<T>& a, hipS
 // Whether level L (RESTRICT_SOLVE: the coarse level) is small enough for the
 // operation's block form.  The other forms solve a column in two lanes, which
 // only pays once the level's columns fill the GPU; measured on MI355X, FP64,
-// 128 layers, in us, block form / other form: Smooth 64^2 9.4 / 22.9, 128^2
-// 21 / 24, 256^2 84 / 57; line solve 64^2 8.4 / 12.4, 128^2 15 / 13 (64 layers
-// 7.5 / 8.2); residual + restriction + line solve onto 64^2 10 / 24, onto 128^2
-// 48 / 45 (64 layers 25 / 34), onto 256^2 183 / 150.  Fields must stay within
-// 32-bit byte offsets.
+// 128 layers, in us, block form / other form: Smooth 64^2 9.1 / 19.7, 128^2
+// 21 / 24, 256^2 84 / 57; line solve 64^2 8.3 / 11.3, 128^2 15 / 13 (64 layers
+// 7.5 / 7.3); CG step 64^2 14.4 / 19.4, 92 x 88 17.6 / 20.1.  Residual +
+// restriction + line solve, a cycle of two levels with them in one launch / in
+// two: onto 64^2 74 / 83, 128^2 155 / 162, 64 layers 40 / 47 and 82 / 87, 8
+// layers 16 / 20 and 21 / 23; FP32 at 65 and 128 layers from 96^2 on within 1.4
+// of each other.  With few layers the lines are the same: 2 layers, 128^2, two
+// sweeps FP64 7.8 / 7.6, FP32 6.3 / 6.3, line solve 3.0 / 3.1, cycle 15.6 / 18.6.
+// FP32 smoothing of exactly 128 layers, where the other form has no virtual
+// rows, ends at 8192 columns (two sweeps 92 x 88 20.3 / 25.0, 104^2 26.0 / 25.2,
+// 128^2 26.3 / 25.3; 100 layers 25.3 / 28.6).  Fields must stay within 32-bit
+// byte offsets.
 template <typename T>
 bool block_fits(BlockOp op, const Lvl<T>& L) {
   const int64_t cols = (int64_t)L.nx * L.ny;
-  const int64_t most = op == BlockOp::CG || (op == BlockOp::SOLVE && L.nz > 64)
+  const bool smooth = op == BlockOp::SMOOTH || op == BlockOp::SMOOTH_NORM;
+  const int64_t most = op == BlockOp::CG || (op == BlockOp::SOLVE && L.nz > 64) ||
+                               (smooth && sizeof(T) == 4 && L.nz == 128)
                            ? kBlockMaxCols / 2
                        : op == BlockOp::PROLONG_SMOOTH && sizeof(T) == 4 && L.nz <= 64
                            ? 2 * kBlockMaxCols

@@ -77,7 +77,7 @@ SOLVES = ("mg_f64", "pcg_f64", "mg_mixed", "fcg_mixed")
 # HBM traffic per launch of a kernel, from two rocprofv3 --pmc passes
 # (FETCH_SIZE, then WRITE_SIZE; KiB per dispatch averaged over the kernel's
 # dispatches) scaled by what the same counters read for a plain copy of known
-# size.  Reported only while the kernel source hashes to the recorded value.
+# size.  Reported only while the kernel's sources hash to the recorded value.
 MEASURED_TRAFFIC = {
     # k_cg_p1 (both forms), 64x8 workgroups, tile groups of 8 (the stored
     # launch shape); profiles/cg_p1_1024x1024x128_pmc.md.  Averages over the
@@ -94,7 +94,9 @@ MEASURED_TRAFFIC = {
         "shape": [8, 8],
     },
 }
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1402_3545_amd", "csrc", "kernels.hip")
+# the kernel's source and the library's headers that its device code comes from
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1402_3545_amd", "csrc", f)
+                  for f in ("kernels.hip", "device_common.h", "gmg_internal.h")]
 COPY_PROBE_BYTES = 2 << 30   # per direction
 
 
@@ -116,8 +118,11 @@ def algorithmic_bytes(kernel, level, prec, w):
 
 def source_sha256():
     import hashlib
-    with open(KERNEL_SOURCE, "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SOURCES:
+        with open(path, "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
 
 
 def measured_traffic(key, shape):

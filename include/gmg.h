@@ -283,7 +283,7 @@ int gmg_transpose_out(gmg_ctx *c, int level, int prec, const void *src_x, void *
  * refinement with FP32 cycles when the context's preconditioner is FP32) or
  * pcg_solve (method 1: line preconditioner, 2: V-cycle preconditioner,
  * flexible CG), converts u back and copies it into u_host.  The copies go
- * through two pinned host buffers of up to 128 MiB, in chunks: host threads
+ * through two pinned host buffers of up to 16 MiB, in chunks: host threads
  * fill (or empty) one buffer while the DMA engine drains (or fills) the other.
  * On first use the context allocates three level-0 FP64 device fields and
  * the two pinned buffers, and keeps them until gmg_destroy (GMG_ENOMEM when

@@ -190,7 +190,8 @@ int build(Batch* b, hipStream_t s) {
       int nb;
       if (cb) {
         nb = (it.L.nx * it.L.ny + cb - 1) / cb;
-      } else if (kind == GKind::LINE_SOLVE || kind == GKind::SMOOTH || kind == GKind::PROLONG_SMOOTH) {
+      } else if (kind == GKind::LINE_SOLVE || kind == GKind::SMOOTH ||
+                 kind == GKind::PROLONG_SMOOTH) {
         nb = it.nti * it.ntj;
       } else if (kind == GKind::RESRESTRICT) {
         nb = it.nti * it.ntj * (int)stencil_tiles_k(it.X.nz);

@@ -115,7 +115,7 @@ struct Shape {
 constexpr int kMaxLevels = 20;
 
 // largest number of columns of a level whose smoothers take the block form
-// (line_block.h)
+// (line_block.h; half or twice of it for some kernels, see block_fits)
 constexpr int64_t kBlockMaxCols = 16384;
 
 // Slot of (kernel kind, level, precision) in the per-context tables.
@@ -313,7 +313,7 @@ hipError_t launch_restrict_smooth(const Lvl<T>& C, const Lvl<T>& F, const T* rf,
 template <typename T>
 hipError_t launch_line_solve_scaled(const Lvl<T>& L, const T* r, T* z, T scale, hipStream_t s, Shape sh = {});
 
-// Smooth that also returns ||f - A u_in||^2 per workgroup (line_blocks partials)
+// Smooth that also returns ||f - A u_in||^2 per workgroup (*nblocks partials)
 template <typename T>
 hipError_t launch_smooth_norm(const Lvl<T>& L, const T* f, const T* uin, T* uout, T rho,
                               double* partials, int64_t* nblocks, hipStream_t s, Shape sh = {});

@@ -170,10 +170,11 @@ __device__ __forceinline__ void walk(P& pol, int n) {
 
 // Whether layer k0, the first of a segment, sums its east product before its
 // west one: the first layer of a level's last, partial run of KSEG layers, in
-// tiles without the lane exchange.  Any order would do; but flexible CG and the
-// refinement hand these residuals to FP32 cycles, which on ill-conditioned
-// columns turn another last bit into a difference of 1e-9 to 1e-7 of the
-// solution, so every segment length keeps the one order.
+// tiles without the lane exchange.  Neither order is the more accurate one; but
+// flexible CG and the refinement hand these residuals to FP32 cycles, which on
+// ill-conditioned columns turn another last bit into a difference of 1e-9 to
+// 1e-7 of the solution, so every segment length keeps the order that segments
+// of KSEG layers were first compiled to.
 __device__ __forceinline__ bool east_first(int k0, int nz) {
   return k0 % KSEG == 0 && k0 + KSEG > nz;
 }
@@ -1896,7 +1897,8 @@ __global__ __launch_bounds__(64 * SR) void k_fcg_update(Lvl<double> L, double* _
 // EX: every item of the launch has columns of exactly 2 HALF layers (the host
 // checks), so the exact-height form serves them all.
 template <int HALF, int MODE, bool EX>
-__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(3))) void k_line_grouped(const GItem<float>* __restrict__ items,
+__global__ __launch_bounds__(NTHREADS)
+__attribute__((amdgpu_waves_per_eu(3))) void k_line_grouped(const GItem<float>* __restrict__ items,
                                                            int nitems,
                                                            const int* __restrict__ active,
                                                            float rho) {
@@ -2229,9 +2231,8 @@ __global__ __launch_bounds__(NTHREADS) void k_pcg_final_update(Lvl<double> L,
   }
 }
 
-// dst = src over a level's field (both in its layout), gated like the
-// iteration it belongs to
-// dst = src, whole field.  Bound by bytes on large levels, by the dispatch of
+// dst = src over a level's whole field (both in its layout), gated like the
+// iteration it belongs to.  Bound by bytes on large levels, by the dispatch of
 // workgroups on small ones: a workgroup of one value a thread moved 8 MB in 12
 // us.  Each thread takes COPY_WORDS 16-byte words, all loaded before the first
 // is stored (fields and their rows start at multiples of 16 bytes).  A smoothing
@@ -2315,7 +2316,7 @@ hipError_t line_dispatch(const Lvl<T>& L, const LineArgs<T>& a, hipStream_t s, i
     }
   }
   if constexpr (MODE != LINE_RESTRICT_SMOOTH) {
-    // levels with few columns: eight wavefronts per 32 columns
+    // levels with few columns: eight wavefronts per 8, 16 or 32 columns
     if (block_fits(block_op<MODE>(), L)) {
       BlockArgs<T> q;
       q.a = a.a;
@@ -2462,13 +2463,20 @@ hipError_t launch_pair_reduce(PairState* ps, int* active, const double* partials
 // segment, not by bandwidth, and four times the workgroups overlap those
 // waits; on larger levels the layers read twice at the segments' ends cost
 // more.  The line differs by kernel (us, KSEG / KSHORT at the given number of
-// KSEG workgroups, FP64): residual 15 / 12 at 20, 42 / 45 at 1024; CG direction
-// 12 / 6 at 20, 18.6 / 19.5 at 256; residual + restriction 11 / 4 at 5, 53 / 45
-// at 384, 30 / 31 at 512 (128 layers), 317 / 328 at 1400; prolongation 41 / 35
-// at 1152, 50 / 48 at 1536, 75 / 75 at 2304; refinement update 10 / 5 at 20, 15
-// / 16 at 240.  The flexible-CG kernels keep KSEG: their dot products steer an
-// FP32 cycle, which magnifies another order of summation on ill-conditioned
-// columns (3.6e-8 of the solution on a flat box of 60^2 x 32).
+// KSEG workgroups, FP64, 128 layers unless given): residual 8.4 / 4.6 at 64, 9.8
+// / 7.0 at 128, 11.6 / 12.8 at 256, 20.2 / 18.5 at 384, 41 / 44 at 1024; CG
+// direction 17 / 11 at 64, 24 / 22 at 192, 26.8 / 29.0 at 256, 40 / 35 at 384,
+// 87 / 86 at 1024; refinement update 14.4 / 9.6 at 64, 17.8 / 13.2 at 128, 20.7
+// / 23.1 at 256, 48 / 54 at 768; prolongation 7.8 / 3.9 at 64, 16.6 / 14.0 at
+// 384, 27.3 / 26.5 at 768, 45 layers 51 / 42 at 1536, 79 / 79 at 2304; a cycle
+// of two levels with the restriction 88 / 83 at 64, 112 / 105 at 128, 240 / 232
+// at 384, 285 / 293 at 480, 64 layers 233 / 225 at 384, 436 / 438 at 768.
+// Between a line and the count from which short segments always lose, they win
+// where KSEG workgroups just miss a round of the CUs (residual, 64 layers, 19.5
+// / 15.2 at 288) and lose where they just fill one (256).  The flexible-CG
+// kernels keep KSEG: their dot products steer an FP32 cycle, which magnifies
+// another order of summation on ill-conditioned columns (3.6e-8 of the solution
+// on a flat box of 60^2 x 32).
 constexpr int KSHORT = 8;
 constexpr int kSegResidual = 128, kSegCg = 192, kSegRestrict = 1024, kSegProlong = 2048,
               kSegCorrect = 128;
@@ -2652,10 +2660,9 @@ hipError_t launch_smooth_norm(const Lvl<T>& L, const T* f, const T* uin, T* uout
   a.rho = rho;
   a.partials = partials;
   const int rows = smooth_rows(L, sh);
-  const int64_t nb = block_fits(BlockOp::SMOOTH_NORM, L) ? block_count(L.nx, L.ny)
-             : (rows == 3 && line_w2_fits(L)) ? (int64_t)(L.nx / 64) * (L.ny / 2)
+  *nblocks = block_fits(BlockOp::SMOOTH_NORM, L) ? block_count(L.nx, L.ny)
+             : (rows == 3 && line_w2_fits(L))   ? (int64_t)(L.nx / 64) * (L.ny / 2)
                                                 : line_blocks(L.nx, L.ny);
-  *nblocks = nb;
   return line_dispatch<T, LINE_SMOOTH_NORM>(L, a, s, sh.group, rows);
 }
 
@@ -2665,8 +2672,8 @@ hipError_t launch_resrestrict(const Lvl<T>& F, const Lvl<T>& C, const T* u, cons
   return with_rows(sh.rows, stencil_seg(C.nx, C.ny, C.nz, kSegRestrict), [&](auto R, auto K) {
     constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
     const int nti = cdiv(C.nx, 64), ntj = cdiv(C.ny, SR), nkb = cdiv(C.nz, KS);
-    hipLaunchKernelGGL((k_resrestrict<T, SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, F, C, u, f, fc, nti, ntj,
-                       sh.group);
+    hipLaunchKernelGGL((k_resrestrict<T, SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, F,
+                       C, u, f, fc, nti, ntj, sh.group);
   });
 }
 
@@ -2677,8 +2684,8 @@ hipError_t launch_correct_residual(const Lvl<double>& L, const double* u, const 
     constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
     const int nti = cdiv(L.nx, 64), ntj = cdiv(L.ny, SR), nkb = cdiv(L.nz, KS);
     *nblocks = (int64_t)nti * ntj * nkb;
-    hipLaunchKernelGGL((k_correct_residual<SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, L, u,
-                       e, f, uout, r32, partials, nti, ntj, sh.group);
+    hipLaunchKernelGGL((k_correct_residual<SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s,
+                       L, u, e, f, uout, r32, partials, nti, ntj, sh.group);
   });
 }
 
@@ -2695,8 +2702,8 @@ hipError_t launch_prolongate(const Lvl<T>& C, const Lvl<T>& F, const T* uc, T* u
   return with_rows(sh.rows, seg, [&](auto R, auto K) {
     constexpr int SR = decltype(R)::value, KS = decltype(K)::value;
     const int nti = cdiv(F.nx, 64), ntj = cdiv(F.ny, SR), nkb = cdiv(F.nz, KS);
-    hipLaunchKernelGGL((k_prolongate<T, SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, C, F, uc, uf, nti, ntj,
-                       sh.group);
+    hipLaunchKernelGGL((k_prolongate<T, SR, KS>), dim3(nti * ntj * nkb), dim3(64 * SR), 0, s, C,
+                       F, uc, uf, nti, ntj, sh.group);
   });
 }
 
@@ -2726,9 +2733,7 @@ hipError_t launch_cg_p2(const Lvl<double>& L, double* r, const double* q, double
   a.st = st;
   a.init = init;
   a.partials = partials;
-  const int64_t nb =
-      block_fits(BlockOp::CG, L) ? block_count(L.nx, L.ny) : line_blocks(L.nx, L.ny);
-  *nblocks = nb;
+  *nblocks = block_fits(BlockOp::CG, L) ? block_count(L.nx, L.ny) : line_blocks(L.nx, L.ny);
   return line_dispatch<double, LINE_CG>(L, a, s, sh.group);
 }
 
@@ -2868,7 +2873,7 @@ hipError_t launch_add_f32_to_f64(double* u, const float* e, int64_t n, hipStream
   template hipError_t launch_line_solve_scaled<T>(const Lvl<T>&, const T*, T*, T, hipStream_t, \
                                                   Shape);                                     \
   template hipError_t launch_smooth_norm<T>(const Lvl<T>&, const T*, const T*, T*, T, double*, \
-                                            int64_t*, hipStream_t, Shape);               \
+                                            int64_t*, hipStream_t, Shape);                    \
   template hipError_t launch_resrestrict<T>(const Lvl<T>&, const Lvl<T>&, const T*, const T*, \
                                             T*, hipStream_t, Shape);
 

@@ -6,10 +6,10 @@
 // issue of every row's loads and arithmetic in turn.  Here eight wavefronts
 // share CB columns.  Seven form the right-hand sides of all rows at once, a few
 // rows each; meanwhile the eighth eliminates the matrix, whose pivots do not
-// depend on the right-hand side, and keeps their reciprocals.
-// What is left in sequence is one multiply-add and one product a row inwards
-// and one multiply-add a row back, on values that wait in LDS; then the other
-// wavefronts store.
+// depend on the right-hand side, and keeps their reciprocals (in registers, in
+// LDS where block_lds says so).  What is left in sequence is one multiply-add
+// and one product a row inwards and one multiply-add a row back, on right-hand
+// sides that wait in LDS; then the other wavefronts store.
 //
 // CB is 8, 16 or 32: the fewest columns with which the workgroups still find a
 // compute unit each (256 of them).  Fewer columns spread the right-hand sides
@@ -20,10 +20,13 @@
 // and 24 + 12).
 //
 // The elimination runs from both ends of a column (one lane
-// upwards, one downwards), on columns padded to 2 * HALF rows with identity rows, and
-// every operation and its order are those of the 32-column kernels of a
-// larger level: the same values bit for bit.  (The CG step stores r - alpha q
-// itself, where the larger kernel rebuilds it from the elimination.)
+// upwards, one downwards), on columns padded to 2 * HALF rows with identity
+// rows, and every operation and its order are those of the padded 32-column
+// kernels of a larger level: the same values bit for bit.  Two differ by
+// rounding: the FP64 smoothers at heights other than 32, 64 and 128, which on a
+// larger level meet in the middle of the real rows, and the CG step, which
+// stores r - alpha q itself, where the larger kernel rebuilds it from the
+// elimination.
 #pragma once
 
 #include "device_common.h"
@@ -351,7 +354,7 @@ __device__ __forceinline__ void block_body(const Lvl<T>& L, const BlockArgs<T>& 
       }
     }
   } else {
-    // the pivots of both halves of the 32 columns
+    // the pivots of both halves of the CB columns
     __syncthreads();
     const BlockProf<T>* pt = s_t[hs];
     T cprev = T(0);

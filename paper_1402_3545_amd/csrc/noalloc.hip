@@ -19,7 +19,8 @@
 namespace {
 
 // 1 MiB: the partial sums of a residual launch (one FP64 value per workgroup;
-// the smallest stencil workgroup covers 64 columns x 4 rows x 32 layers).
+// a stencil workgroup covers at least 64 columns x 4 rows x 32 layers, or 8
+// layers on levels that then still have less than a thousand of them).
 constexpr int64_t kScratchDoubles = 131072;
 __device__ __align__(256) double scratch[kScratchDoubles];
 
@@ -72,8 +73,9 @@ int gmg_residual_noalloc(gmg_ctx* c, int level, int prec, const void* f, const v
   if (norm2 && reinterpret_cast<uintptr_t>(norm2) % 8)
     return gmg::set_error(GMG_EINVAL, "norm2 not 8-byte aligned");
   const gmg::LevelBuf& B = c->lev[level];
-  // every stencil launch shape has at least 4 rows, so this bounds the
-  // workgroup count of the residual launch
+  // every stencil launch shape has at least 4 rows, and stencil_blocks counts
+  // the segments of the kernel with the most, so this bounds the workgroup
+  // count of the residual launch
   if (norm2 && gmg::stencil_blocks(B.nx, B.ny, B.nz) > kScratchDoubles)
     return gmg::set_error(GMG_EINVAL,
                           "level too large for the static scratch (more than 131072 residual "

@@ -153,3 +153,57 @@ def test_pcg_at_ragged_heights(grid, bc_h):
     assert st == st_ref == 0 and it == it_ref
     np.testing.assert_allclose(hist, hist_ref, rtol=1e-6, atol=1e-14)
     assert max_rel(ctx.from_device(ud), u_ref, np.abs(u_ref).max()) < 1e-9
+
+
+# the line solve keeps two lanes a column above 8192 columns and 64 layers, and
+# above 16384 columns throughout
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("grid", [(100, 90, 65), (100, 90, 70), (100, 90, 127), (100, 90, 128),
+                                  (136, 130, 37), (WX, WY, 64)])
+def test_tile_orders_of_the_line_kernels(grid, prec):
+    """Line solve and smoother in every tile order: bitwise the same values, and
+    the oracle's."""
+    import paper_1402_3545_amd as G
+    nx, ny, nz = grid
+    ctx, orc, _ = problem(nx, ny, nz, seed=115)
+    f, u, fd, u0 = _inputs(ctx, 115, nx * ny * nz, prec)
+    outs = []
+    for group in (0, 1, 2, 8):
+        G.gmg_set_launch(ctx, "line_solve", 0, prec, 4, group)
+        zd = ctx.empty(dtype=fd.dtype)
+        G.line_solve(ctx, 0, fd, zd)
+        res = [ctx.from_device(zd)]
+        for rows in (4, 2):
+            G.gmg_set_launch(ctx, "smooth", 0, prec, rows, group)
+            ud = u0.clone()
+            G.line_smooth(ctx, 0, fd, ud, nsweeps=2)
+            res.append(ctx.from_device(ud))
+        outs.append(res)
+    for res in outs:
+        assert np.array_equal(res[0], outs[0][0])
+        assert np.array_equal(res[1], outs[0][1]) and np.array_equal(res[2], outs[0][1])
+    bar = 1e-12 if prec == 0 else f32_line_bar(nz)
+    ref = orc.line_solve(f)
+    assert max_rel(outs[0][0], ref, np.abs(ref).max()) < bar
+    ref = orc.smooth(f, orc.smooth(f, u))
+    assert max_rel(outs[0][1], ref, np.abs(ref).max()) < 2 * bar
+
+
+@pytest.mark.parametrize("nz", [37, 64])
+def test_tile_orders_of_the_cg_step(nz):
+    """Line-PCG with its preconditioner step in every tile order: the same
+    iteration count, the solutions equal to the rounding of its dot products
+    (which group other columns)."""
+    import paper_1402_3545_amd as G
+    nx, ny = 136, 130
+    ctx, orc, _ = problem(nx, ny, nz, seed=117)
+    f = W.rhs(117, 0, nx, ny, nz)
+    fd = ctx.to_device(f)
+    u_ref, it_ref, hist_ref, _, st_ref = orc.pcg_solve(f, rtol=1e-8, maxit=500)
+    for group in (0, 1, 2, 8):
+        G.gmg_set_launch(ctx, "cg_tridiag", 0, G.GMG_F64, 4, group)
+        ud = ctx.empty()
+        it, rel, hist, st = G.pcg_solve(ctx, fd, ud, rtol=1e-8, maxit=500)
+        assert st == st_ref == 0 and it == it_ref
+        np.testing.assert_allclose(hist, hist_ref, rtol=1e-6, atol=1e-14)
+        assert max_rel(ctx.from_device(ud), u_ref, np.abs(u_ref).max()) < 1e-9

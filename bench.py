@@ -83,14 +83,14 @@ MEASURED_TRAFFIC = {
     # launch shape); profiles/cg_p1_1024x1024x128_pmc.md.  Averages over the
     # 162 dispatches that did the work (82 odd-iteration, 80 even-iteration
     # forms; the two enqueued past convergence return at once).  Plain-copy
-    # calibration: 2 GiB read + 2 GiB written read FETCH_SIZE 1048592.4 KiB,
-    # WRITE_SIZE 2097184.7 KiB.
+    # calibration: 2 GiB read + 2 GiB written read FETCH_SIZE 1048592.8 KiB,
+    # WRITE_SIZE 2097194.0 KiB.
     ("cg_spmv", 0, "f64"): {
-        "fetch_kib": 2249894.2955,
-        "write_kib": 2615227.7147,
-        "copy_fetch_scale": 2097152.0 / 1048592.3646,
-        "copy_write_scale": 2097152.0 / 2097184.7083,
-        "source_sha256": "82d7e5e79a7e2605548a24ed7ca2dd08aac22bdfcedca014d8d9845f19d38090",
+        "fetch_kib": 2250382.2006,
+        "write_kib": 2615227.8650,
+        "copy_fetch_scale": 2097152.0 / 1048592.8229,
+        "copy_write_scale": 2097152.0 / 2097194.0000,
+        "source_sha256": "8ee4fcccc6d129149396f825333dbb7a80370835bec1031dd18e26dfc2120cca",
         "shape": [8, 8],
     },
 }

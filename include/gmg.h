@@ -343,8 +343,8 @@ int gmg_solve_host(gmg_ctx *c, int method, const double *f_host, double *u_host,
  * gmg_set_launch / gmg_get_launch: one entry of the context's table;
  * GMG_EINVAL for a bad kernel id, level or precision, rows not in {4, 8, 16}
  * (or 1 for the line solve and smoother, 2 or 3 for the smoother;
- * GMG_K_PROLONG_SMOOTH takes 4, 2 or 3 only), group outside [0, 4096], and for
- * batched contexts.
+ * GMG_K_PROLONG_SMOOTH takes 4, 2 or 3 only, GMG_K_RESTRICT_SOLVE none), group
+ * outside [0, 4096], and for batched contexts.
  * gmg_autotune: for every level and for the precisions the context's solvers
  * use, runs each candidate shape (rows 4/8/16, 4/1 or 4/1/2/3, group 0/1/2/4/8) of
  * each kernel kind `reps` times on the context's own work buffers (their contents are
